@@ -148,6 +148,8 @@ def kernel_source(kernel):
         return "jacobi_march.hip"
     if kernel.startswith("gs_wave"):
         return "gauss_seidel.hip"
+    if kernel.startswith("gs_pipe"):
+        return "gs_pipe.h"
     if ("allencahn" in kernel or kernel.startswith("ac_march")) and os.path.exists(
             os.path.join(ROOT, "paper_2509_02197_amd", "csrc", "allencahn.hip")):
         return "allencahn.hip"
@@ -226,7 +228,8 @@ def run_workload(adst, torch, w, opts, steps, warmup, traced_calls, say, inp=Non
     prob = adst.make_problem(w.kind, w.dtype, dims_of(w.shape), w.params, flags, lim)
     grads = (adst.ADST_GRAD_COEFF if w.want_dK else 0) | (adst.ADST_GRAD_PARAMS if want_dp else 0)
     info = adst.adst_plan(prob, w.steps, budget, sched, grads)
-    ws = torch.empty(info.workspace_bytes, dtype=torch.uint8, device=dev)
+    ws = torch.empty(info.workspace_bytes + adst.adst_sweep_workspace_bytes(prob, w.steps),
+                     dtype=torch.uint8, device=dev)
     dx0 = torch.empty_like(x0)
     dK = torch.empty_like(x0) if w.want_dK else None
     L = torch.empty((), dtype=torch.float64, device=dev)
@@ -516,8 +519,8 @@ def rocprof_label(name):
         return f"jacobi_march<{'adj' if t(2) else 'fwd'},{targs[1]}>"
     if base == "jacobi_lim_adjoint":   # <R, VEC, DP>
         return "jacobi_lim_adjoint<dp>" if t(2) else "jacobi_lim_adjoint"
-    if base == "gs_wave":              # <R, ADJ, VEC>
-        return "gs_wave<adj>" if t(1) else "gs_wave<fwd>"
+    if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>
+        return base + ("<adj>" if t(1) else "<fwd>")
     if base == "ac_march":             # <R, NF, ADJ, RR, ZC, DA, ST, NT>
         if t(2):
             return "ac_march<adj>" if targs[1] == "0" else f"ac_march<fwd{targs[1]}+adj>"

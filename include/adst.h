@@ -221,8 +221,9 @@ typedef struct {
   int64_t n_actions;        /* length of the action list */
   int64_t fwd_launches;     /* forward actions (a fused or a pipelined run counts once) */
   int64_t adj_launches;     /* adjoint actions (likewise) */
-  int64_t fwd_kernels;      /* forward kernel dispatches the actions enqueue */
-  int64_t adj_kernels;      /* adjoint kernel dispatches the actions enqueue */
+  int64_t fwd_kernels;      /* forward kernel dispatches the actions enqueue (the in-place kind:
+                               wavefront levels, one dispatch each in level launches) */
+  int64_t adj_kernels;      /* adjoint kernel dispatches the actions enqueue (likewise) */
   uint64_t state_bytes;     /* bytes of one state */
   uint64_t budget_bytes;    /* the budget passed in */
   uint64_t slot_bytes_peak; /* slots * state_bytes: checkpoint storage actually used */
@@ -270,13 +271,25 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
                               int32_t sched, int32_t grads, adst_action* out, int64_t cap,
                               int64_t* n_out);
 
+/* Bytes of workspace, beyond workspace_bytes (adst_vjp) or
+ * fwd_workspace_bytes (adst_forward), with which the in-place kind's sweeps
+ * run as one persistent launch per 256 sweeps instead of one launch per
+ * wavefront level (400 x 400 f64, 100 sweeps and their reverse: 7.4 ms with
+ * level launches). Optional: a call given less, or given a ws whose part
+ * beyond workspace_bytes overlaps one of its arrays, runs the level launches;
+ * the results are the same bit for bit. About half a state of 8-byte values
+ * (a whole one of 4-byte values) plus a few percent. 0 for the other kinds, for
+ * steps <= 0 and for an invalid problem (no error is recorded). Host only. */
+uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps);
+
 /* x_T after `steps` forward steps: the unmodified program whose gradient
  * adst_vjp computes (Sec. I: the user's program is differentiated without
  * modification; the step kinds are defined at the top of this file).
  * x0 and xT are [nz][ny][nx] arrays of the working precision; coeff is K for
  * VARDIFF2D9 and must be NULL-or-ignored otherwise. ws must hold
  * adst_plan_info.fwd_workspace_bytes (one state when steps >= 2, else 0;
- * always 0 for the in-place kind, which runs in xT).
+ * always 0 for the in-place kind, which runs in xT and uses ws only as
+ * adst_sweep_workspace_bytes says).
  * Errors: as adst_plan, plus ADST_ERR_WORKSPACE and ADST_ERR_HIP. */
 adst_status adst_forward(const adst_problem* prob, const void* x0, const void* coeff,
                          int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
@@ -408,7 +421,7 @@ typedef struct {
   int32_t phase;          /* 0 forward sweep, 1 recomputation, 2 adjoint, 3 loss and seed,
                              4 the constants' final sum (the phase of its first launch) */
   int32_t reserved;
-  int64_t launches;       /* kernel dispatches */
+  int64_t launches;       /* kernel dispatches (the in-place kind: wavefront levels) */
   double ms_sum;          /* summed duration (ms) */
   double ms_min, ms_max;  /* per dispatch (a pipelined sequence: its average dispatch) */
   double alg_bytes_sum;   /* algorithmic bytes of all those dispatches */

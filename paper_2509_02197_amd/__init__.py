@@ -28,7 +28,7 @@ ADST_BUF_NONE, ADST_BUF_X0, ADST_BUF_W0, ADST_BUF_W1, ADST_BUF_XT, ADST_BUF_SLOT
 
 EXPORTED = ("adst_plan", "adst_plan_actions", "adst_forward", "adst_vjp", "adst_ilp_solve",
             "adst_trace_kernels", "adst_copy", "adst_vjp_static_ws", "adst_status_str",
-            "adst_last_error")
+            "adst_last_error", "adst_sweep_workspace_bytes")
 ADST_STATIC_WS_BYTES = 64 << 20
 PHASE_NAMES = ("forward sweep", "recomputation", "adjoint", "loss and seed", "constants")
 ILP_EVENTS = {"alloc": 0, "free": 1, "produce": 2, "drop": 3, "recompute": 4,
@@ -121,6 +121,8 @@ def lib():
     for f in ("adst_plan", "adst_plan_actions", "adst_forward", "adst_vjp", "adst_ilp_solve",
               "adst_trace_kernels", "adst_copy", "adst_vjp_static_ws"):
         getattr(L, f).restype = ctypes.c_int
+    L.adst_sweep_workspace_bytes.argtypes = [P(adst_problem), i32]
+    L.adst_sweep_workspace_bytes.restype = u64
     L.adst_status_str.argtypes = [ctypes.c_int]
     L.adst_status_str.restype = ctypes.c_char_p
     L.adst_last_error.argtypes = []
@@ -193,6 +195,12 @@ def adst_plan_actions(prob, steps, mem_budget_bytes, sched, grads=0):
     _check(L.adst_plan_actions(ctypes.byref(prob), steps, mem_budget_bytes, sched,
                                int(grads), buf, n.value, ctypes.byref(n)))
     return [(a.op, a.t, a.src, a.dst, a.n) for a in buf[:n.value]]
+
+
+def adst_sweep_workspace_bytes(prob, steps):
+    """Workspace beyond the plan's with which the in-place kind's sweeps run
+    as one launch (0 for the other kinds)."""
+    return int(lib().adst_sweep_workspace_bytes(ctypes.byref(prob), steps))
 
 
 def adst_forward(prob, x0, coeff, steps, xT, ws, ws_bytes, stream=None):
@@ -307,6 +315,33 @@ def _check_tensors(x0, **others):
         raise ValueError(f"x0 must be on a GPU, not {x0.device}")
 
 
+def _workspace(ws, need, prob, steps, device, stream):
+    """(the workspace a call runs in, the one it hands back): ws where it
+    holds `need` bytes, else a new one. The in-place kind's calls run in one
+    with adst_sweep_workspace_bytes more, taken from torch's allocator where
+    ws is smaller and that much is free."""
+    import torch
+    extra = adst_sweep_workspace_bytes(prob, steps) if prob.kind == ADST_GAUSSSEIDEL2D5 else 0
+    given = ws is not None and ws.numel() >= need
+    if given and ws.numel() >= need + extra:
+        return ws, ws
+    roomy = None
+    if extra:
+        try:
+            roomy = torch.empty(need + extra, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    if roomy is not None and stream is not None:
+        # released to the allocator only when the stream it is used on is done
+        handle = _stream(stream)
+        roomy.record_stream(torch.cuda.ExternalStream(handle, device=device) if handle
+                            else torch.cuda.default_stream(device))
+    if not given:
+        ws = roomy if roomy is not None else torch.empty(max(need, 1), dtype=torch.uint8,
+                                                         device=device)
+    return (roomy if roomy is not None else ws), ws
+
+
 def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, flags=0):
     """x_T on the device of x0 (torch tensors, row-major)."""
     import torch
@@ -314,8 +349,8 @@ def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, f
     prob = make_problem(kind, _dtype_code(x0), _dims(x0.shape), params, flags, lim)
     xT = torch.empty_like(x0)
     info = adst_plan(prob, steps, 1 << 62, ADST_SCHED_STORE_ALL)
-    ws = torch.empty(max(info.fwd_workspace_bytes, 1), dtype=torch.uint8, device=x0.device)
-    adst_forward(prob, x0, coeff, steps, xT, ws, info.fwd_workspace_bytes, stream)
+    ws, _ = _workspace(None, info.fwd_workspace_bytes, prob, steps, x0.device, stream)
+    adst_forward(prob, x0, coeff, steps, xT, ws, ws.numel(), stream)
     return xT
 
 
@@ -335,13 +370,12 @@ def vjp(kind, x0, coeff=None, steps=1, loss=ADST_LOSS_HALF_SQ, aux=None, budget_
         budget_bytes = (1 << 63)
     grads = (ADST_GRAD_COEFF if want_dcoeff else 0) | (ADST_GRAD_PARAMS if want_dparams else 0)
     info = adst_plan(prob, steps, budget_bytes, sched, grads)
-    if ws is None or ws.numel() < info.workspace_bytes:
-        ws = torch.empty(info.workspace_bytes, dtype=torch.uint8, device=x0.device)
+    run_ws, ws = _workspace(ws, info.workspace_bytes, prob, steps, x0.device, stream)
     dx0 = torch.empty_like(x0)
     dK = torch.empty_like(x0) if want_dcoeff else None
     xT = torch.empty_like(x0) if want_xT else None
     L = torch.empty((), dtype=torch.float64, device=x0.device)
     dp = torch.empty(2, dtype=torch.float64, device=x0.device) if want_dparams else None
     info = adst_vjp(prob, x0, coeff, steps, loss, aux, budget_bytes, sched, dx0, dK, xT, L, dp,
-                    ws, ws.numel(), stream)
+                    run_ws, run_ws.numel(), stream)
     return {"dx0": dx0, "dK": dK, "xT": xT, "loss": L, "dparams": dp, "info": info, "ws": ws}

@@ -418,6 +418,24 @@ Range range_of(const char* name, const void* p, uint64_t bytes) {
   return {name, lo, p ? lo + bytes : lo};
 }
 
+// The scratch with which the in-place kind's sweeps run as one launch: the
+// part of ws beyond the first `used` bytes, where it is large enough and
+// touches none of the call's arrays (a caller may pass a larger ws_bytes
+// whose tail it uses otherwise); null elsewhere, and the sweeps then run as
+// level launches.
+void* sweep_scratch(const Checked& c, int32_t steps, void* ws, uint64_t used, uint64_t ws_bytes,
+                    const std::vector<Range>& arrays) {
+  if (!c.in_place || !ws || ws_bytes < used) return nullptr;
+  const uint64_t need = gs_pipe_bytes(c.shape, steps);
+  const uintptr_t lo = reinterpret_cast<uintptr_t>(ws) + used, end = lo + (ws_bytes - used);
+  const uintptr_t at = (lo + 127) / 128 * 128;
+  if (need == 0 || at > end || end - at < need) return nullptr;
+  const Range r = {"scratch", at, at + need};
+  for (const Range& a : arrays)
+    if (overlaps(r, a)) return nullptr;
+  return reinterpret_cast<void*>(at);
+}
+
 // Every output range must be disjoint from every other output and from the
 // inputs (inputs may overlap each other: they are only read).
 adst_status check_disjoint(const std::vector<Range>& outs, const std::vector<Range>& ins) {
@@ -604,6 +622,9 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
   if (loss != ADST_LOSS_HALF_SQ) ins.push_back(range_of("loss_aux", loss_aux, S));
   st = check_disjoint(outs, ins);
   if (st != ADST_OK) return st;
+  std::vector<Range> arrays = ins;
+  arrays.insert(arrays.end(), outs.begin(), outs.end());
+  void* const scratch = sweep_scratch(c, steps, ws, L.total, ws_bytes, arrays);
   if (info) fill_info(c, plan, mem_budget_bytes, want_dk, loss, info);
   if (log_level() > 0) log_plan(c, plan, mem_budget_bytes, want_dk, loss);
 
@@ -665,12 +686,12 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
     if (c.in_place && a.op != ADST_OP_SEED) {
       const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
       if (!adj && a.op != ADST_OP_FWD && a.op != ADST_OP_FWDW) return hip_fail(hipErrorInvalidValue, "plan");
-      e = traced(cat, kernel_label(c, a, 1, false),
+      e = traced(cat, scratch ? (adj ? "gs_pipe<adj>" : "gs_pipe<fwd>") : kernel_label(c, a, 1, false),
                  npts * double(a.n) * double(adj ? pp.adj : pp.fwd),
                  [&] {
-                   return adj ? launch_gs_adjoint(c.shape, dx0, a.n, stream)
+                   return adj ? launch_gs_adjoint(c.shape, dx0, a.n, scratch, stream)
                               : launch_gs_forward(c.shape, buffer(a.src), buffer(a.dst), a.n,
-                                                  stream);
+                                                  scratch, stream);
                  },
                  gs_kernel_launches(c.shape, adj, a.n));
       if (e != hipSuccess) return hip_fail(e, "kernel launch");
@@ -818,6 +839,12 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
   return ADST_OK;
 }
 
+uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps) {
+  Checked c;
+  if (check_problem(prob, 0, &c) != ADST_OK || !c.in_place || steps <= 0) return 0;
+  return gs_pipe_bytes(c.shape, steps) + 128;  // and its alignment
+}
+
 adst_status adst_forward(const adst_problem* prob, const void* x0, const void* coeff,
                          int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
                          hipStream_t stream) {
@@ -847,7 +874,10 @@ adst_status adst_forward(const adst_problem* prob, const void* x0, const void* c
     return ADST_OK;
   }
   if (c.in_place) {  // pipelined sweeps from x0 straight into xT
-    e = launch_gs_forward(c.shape, x0, xT, steps, stream);
+    std::vector<Range> arrays = ins;
+    arrays.insert(arrays.end(), outs.begin(), outs.end());
+    e = launch_gs_forward(c.shape, x0, xT, steps,
+                          sweep_scratch(c, steps, ws, 0, ws_bytes, arrays), stream);
     if (e != hipSuccess) return hip_fail(e, "forward sweeps");
     g_last_error.clear();
     return ADST_OK;

@@ -117,12 +117,20 @@ hipError_t launch_finalize(const double* partials, int32_t nparts, double* loss,
 
 // In-place Gauss-Seidel kind: `sweeps` forward sweeps from src into dst
 // (src may equal dst), and `sweeps` reverse sweeps applied to g in place.
-// Each call is a sequence of wavefront launches (gs_kernel_launches of them)
-// that pipelines the sweeps.
+// With scratch (gs_pipe_bytes(s, n) bytes for some n >= sweeps, 128-byte
+// aligned) each runs as one persistent launch per 256 phases (gs_pipe.hip);
+// without (null), as a sequence of wavefront launches, one per level, that
+// pipelines the sweeps. gs_kernel_launches counts the levels.
 hipError_t launch_gs_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
+                             void* scratch, hipStream_t stream);
+hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, void* scratch,
                              hipStream_t stream);
-hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, hipStream_t stream);
 int64_t gs_kernel_launches(const StepShape& s, bool adjoint, int32_t sweeps);
+uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps);
+hipError_t gs_pipe_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
+                           void* scratch, hipStream_t stream);
+hipError_t gs_pipe_adjoint(const StepShape& s, void* g, int32_t sweeps, void* scratch,
+                           hipStream_t stream);
 
 // The limiter's branch outcome at step t: g[c] = 0 wherever the step's
 // unlimited value at c (re-evaluated from x = x_{t-1} with the forward's own
