@@ -20,7 +20,7 @@ namespace {
 
 // ------------------------------------------------------- Allen-Cahn 3-D
 // 2.5-D blocking: a workgroup of 64 x 4 threads owns a 64 x 8 column of the
-// grid over kAcZC planes (two rows per thread) and marches in z. The plane
+// grid over kAcZC planes (fewer on small grids, see z_chunk) (two rows per thread) and marches in z. The plane
 // being updated is staged in LDS with a one-cell xy halo; the planes below
 // and above live in registers, so every input plane is read from HBM once
 // per tile.
@@ -31,7 +31,7 @@ struct AcTile {
 };
 
 __device__ inline bool ac_tile(int nx, int ny, int nz, int tiles_x, int tiles_y, int ntiles,
-                               AcTile* t) {
+                               int zc, AcTile* t) {
   int b = xcd_tile(ntiles);
   if (b >= ntiles) return false;
   t->b = b;
@@ -42,8 +42,8 @@ __device__ inline bool ac_tile(int nx, int ny, int nz, int tiles_x, int tiles_y,
   t->i = t->bx * kAcTX + (int)threadIdx.x;
   t->ja = t->by * kAcTY + (int)threadIdx.y;
   t->jb = t->ja + 4;
-  t->z0 = bz * kAcZC;
-  t->z1 = min(t->z0 + kAcZC, nz);
+  t->z0 = bz * zc;
+  t->z1 = min(t->z0 + zc, nz);
   return true;
 }
 
@@ -73,11 +73,12 @@ template <class R, bool LIM, bool NT>
 __global__ __launch_bounds__(kThreads) void fwd_allencahn3d7(const R* __restrict__ x,
                                                              R* __restrict__ y, int nx, int ny,
                                                              int nz, int tiles_x, int tiles_y,
-                                                             int ntiles, R D, R C, Limit<R> lim) {
+                                                             int ntiles, int zc, R D, R C,
+                                                             Limit<R> lim) {
   auto out = [&](R v) { return LIM ? limited(v, lim) : v; };
   __shared__ R tile[kAcTY + 2][kAcTX + 2];
   AcTile t;
-  if (!ac_tile(nx, ny, nz, tiles_x, tiles_y, ntiles, &t)) return;
+  if (!ac_tile(nx, ny, nz, tiles_x, tiles_y, ntiles, zc, &t)) return;
   const int plane = nx * ny;
   auto ld = [&](int k, int j, int i) -> R {
     return (k >= 0 && k < nz && j >= 0 && j < ny && i >= 0 && i < nx) ? x[k * plane + j * nx + i]
@@ -147,11 +148,10 @@ __global__ __launch_bounds__(kThreads) void fwd_allencahn3d7(const R* __restrict
 // and more of the region evaluated for nothing).
 template <int K>
 constexpr int ac_out_width() { return K == 2 ? 56 : kBX - 2 * (K - 1); }
-template <int K, int RPT, int NZ, int BY>
+template <int K, int RPT, int BY>
 struct AcN {
   static constexpr int SX = kBX, SY = BY * RPT;
   static constexpr int OX = ac_out_width<K>(), OY = SY - 2 * (K - 1);  // output tile
-  static constexpr int ZC = NZ;                               // output planes
   static_assert(OX + 2 * (K - 1) <= SX, "the output tile and its halo fit the region");
 };
 
@@ -161,15 +161,15 @@ struct AcN {
 // 16n). They take the non-temporal hint with the output where states are
 // large (1024^3 call 1890 -> 1875 ms, in one process; 512^3 unchanged): the
 // reverse sweep reads them back, but only after many other launches.
-template <class R, int K, int RPT, int NZ, bool NT, bool ST, int BY>
+template <class R, int K, int RPT, bool NT, bool ST, int BY>
 __global__ __launch_bounds__(kBX * BY) void fwd_allencahn3d7_n(const R* __restrict__ x,
                                                                R* __restrict__ y,
                                                                R* __restrict__ mid0,
                                                                R* __restrict__ mid1, int nx,
                                                                int ny, int nz, int tiles_x,
-                                                               int tiles_y, int ntiles, R D,
-                                                               R C) {
-  using A = AcN<K, RPT, NZ, BY>;
+                                                               int tiles_y, int ntiles, int zc,
+                                                               R D, R C) {
+  using A = AcN<K, RPT, BY>;
   constexpr int SX = A::SX, SY = A::SY, LX = SX + 2, LY = SY + 2, H = K - 1;
   static_assert(K >= 2 && 2 * LX + 2 * SY <= kBX * BY, "ring cells: one per thread");
   static_assert(!ST || K <= 3, "intermediate states go to mid0 (step 1) and mid1 (step 2)");
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kBX * BY) void fwd_allencahn3d7_n(const R* __restri
   const int by = b % tiles_y;
   const int bz = b / tiles_y;
   const int i0 = bx * A::OX, j0 = by * A::OY;
-  const int z0 = bz * A::ZC, z1 = min(z0 + A::ZC, nz);
+  const int z0 = bz * zc, z1 = min(z0 + zc, nz);
   const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kBX + tx;
   const int ic = i0 - H + tx;  // column of this thread
   const int plane = nx * ny;
@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kThreads) void adj_allencahn3d7(const R* __restrict
   __shared__ R tile[kAcTY + 2][kAcTX + 2];
   __shared__ R tilex[DP ? kAcTY + 2 : 1][DP ? kAcTX + 2 : 1];
   AcTile t;
-  if (!ac_tile(nx, ny, nz, tiles_x, tiles_y, ntiles, &t)) return;  // the whole block
+  if (!ac_tile(nx, ny, nz, tiles_x, tiles_y, ntiles, kAcZC, &t)) return;  // the whole block
   DpPrev prev;
   if (DP) prev = dp_prev<2>(dp, t.b);
   const int plane = nx * ny;
@@ -418,12 +418,13 @@ __global__ __launch_bounds__(kThreads) void adj_allencahn3d7(const R* __restrict
 // neighbours), x(k) and x(k+2) at the thread's cells and ring cell stay in
 // registers, so every mask is evaluated from on-chip values and x is read
 // from HBM about once per point.
-template <class R, bool NT, int TW, int ZC>
+template <class R, bool NT, int TW>
 __global__ __launch_bounds__(kBX * TW) void adj_allencahn3d7_lim(const R* __restrict__ x,
                                                                  const R* __restrict__ g,
                                                                  R* __restrict__ gp, int nx,
                                                                  int ny, int nz, int tiles_x,
-                                                                 int tiles_y, int ntiles, R D,
+                                                                 int tiles_y, int ntiles, int zc,
+                                                                 R D,
                                                                  R k0, R k1, R C, Limit<R> lim) {
   constexpr int TY = 2 * TW;                             // tile rows: two per thread
   constexpr int LY = TY + 2, LX = kAcTX + 2;             // g: one-cell ring
@@ -441,8 +442,8 @@ __global__ __launch_bounds__(kBX * TW) void adj_allencahn3d7_lim(const R* __rest
     t.i = t.bx * kAcTX + (int)threadIdx.x;
     t.ja = t.by * TY + (int)threadIdx.y;
     t.jb = t.ja + TW;
-    t.z0 = (b / tiles_y) * ZC;
-    t.z1 = min(t.z0 + ZC, nz);
+    t.z0 = (b / tiles_y) * zc;
+    t.z1 = min(t.z0 + zc, nz);
   }
   const int plane = nx * ny;
   auto in = [&](int k, int j, int i) {
@@ -610,7 +611,7 @@ __global__ __launch_bounds__(kBX * TW) void adj_allencahn3d7_lim(const R* __rest
 constexpr int kMW = 4;
 constexpr uint32_t kOob = 0xFFFFFF00u;  // a buffer offset beyond any plane
 
-template <int NF, int RR, int ZC, int MW = kMW>
+template <int NF, int RR, int MW = kMW>
 struct AcMarch {
   static constexpr int SX = kBX, SY = MW * RR;
   static constexpr int H = NF > 1 ? NF - 1 : 0;  // cells per side the last level loses
@@ -628,7 +629,7 @@ struct AcMarchArgs {
   R* y;        // forward: level NF; ADJ: g_{t-1}
   R* mid0;     // ST: level 1
   R* mid1;     // ST: level 2
-  int nx, ny, nz, tiles_x, tiles_y, ntiles;
+  int nx, ny, nz, tiles_x, tiles_y, ntiles, zc;
   R D, C, k0, k1;
 };
 
@@ -734,7 +735,7 @@ using IC = std::integral_constant<int, N>;
 
 template <class R, int NF, bool ADJ, int RR, int ZC, int DA, bool ST, bool NT, int MW>
 __global__ __launch_bounds__(kBX * MW) void ac_march(AcMarchArgs<R> a) {
-  using M = AcMarch<NF, RR, ZC, MW>;
+  using M = AcMarch<NF, RR, MW>;
   constexpr int H = M::H, SY = M::SY;
   constexpr int NL = NF > 0 ? NF : 1;   // levels kept in rings: 0 .. NL-1
   constexpr int NE = (NF > 0 ? NF : 0) + (ADJ ? 1 : 0);  // exchanged fields
@@ -755,7 +756,7 @@ __global__ __launch_bounds__(kBX * MW) void ac_march(AcMarchArgs<R> a) {
   const int lane = (int)threadIdx.x, w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
   const int c = bx * M::OX - H + lane;      // this lane's column
   const int jw = by * M::OY - H + w * RR;   // this wave's first row
-  const int z0 = bz * ZC, z1 = min(z0 + ZC, a.nz);
+  const int zc = min(a.zc, ZC), z0 = bz * zc, z1 = min(z0 + zc, a.nz);
   const int nx = a.nx, ny = a.ny, nz = a.nz, plane = nx * ny;
   const bool cin = c >= 0 && c < nx;
   // the lanes at the region's sides read the column beyond it (ring), the
@@ -1001,6 +1002,28 @@ inline bool march_fits(const StepShape& s) {
   return int64_t(s.nx) * s.ny * (s.dtype == ADST_F64 ? 8 : 4) < (int64_t(1) << 31);
 }
 
+// Planes per z-chunk of a launch with `cols` tiles in a plane: `most`, halved
+// while the launch has fewer than `want` workgroups, to 16 planes, and then
+// while it has fewer than half of that, to 4: the few planes a workgroup
+// evaluates beyond its chunk weigh little above 16, and below it only a chip
+// with idle CUs gains. Launches of at most `want` workgroups are those of
+// planes too small to fill the chip; with `most` planes in every chunk they
+// ran at the speed of one workgroup (f64, us per three fused steps: 64^3 113
+// -> 15, 128^3 108 -> 23, 256^3 108 -> 90, 384^3 305 -> 277, 512^3 unchanged;
+// store-all call of 12 steps at 128^3 1141 -> 255). Half and twice these
+// counts were within 4% at every size tried. The tiled adjoint with the
+// constants' partials keeps its 32 planes, to which its slots belong.
+constexpr int kWant16 = 1024;  // workgroups of eight or sixteen waves
+constexpr int kWant4 = 2048;   // of four waves
+constexpr int kWantLim = 512;  // the limiter's adjoint (eight waves): at 1024,
+                               // 512^3 took 1% more, at 256, 384^3 29% more
+inline int z_chunk(int64_t cols, int nz, int most, int want) {
+  int zc = most;
+  while (zc > 16 && cols * cdiv(nz, zc) < want) zc /= 2;
+  while (zc > 4 && cols * cdiv(nz, zc) < want / 2) zc /= 2;
+  return zc;
+}
+
 // Rows per wave and planes per chunk of the z-march launches. The plain
 // adjoint (no forward level: few values live per row) runs a 64 x 32 region,
 // as eight waves of four rows, where a plane is kTallPlaneBytes or more: its
@@ -1020,42 +1043,45 @@ hipError_t march(const StepShape& s, const R* x, const R* g, R* y, R* m0, R* m1,
     if (int64_t(s.nx) * s.ny * int64_t(sizeof(R)) >= kTallPlaneBytes)
       return march<R, NF, ADJ, ST, RR, kTallAdjWaves>(s, x, g, y, m0, m1, st);
   }
-  using M = AcMarch<NF, RR, kMarchPlanes, MW>;
+  constexpr int ZC = kMarchPlanes;  // most planes of a chunk
+  using M = AcMarch<NF, RR, MW>;
   const int tx = cdiv(s.nx, M::OX), ty = cdiv(s.ny, M::OY);
-  const int nt = tx * ty * cdiv(s.nz, kMarchPlanes);
+  const int zc = z_chunk(tx * int64_t(ty), s.nz, ZC, MW == kMW ? kWant4 : kWant16);
+  const int nt = tx * ty * cdiv(s.nz, zc);
   const R D = R(s.p0), C = R(s.p1);
-  const AcMarchArgs<R> a{x, g, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt,
+  const AcMarchArgs<R> a{x, g, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc,
                          D, C, R(1) + D * R(-6), R(3) * C};
   const dim3 grid(xcd_grid(nt)), block(kBX, MW);
   if (streams(s))
-    ac_march<R, NF, ADJ, RR, kMarchPlanes, kMarchAhead, ST, true, MW><<<grid, block, 0, st>>>(a);
+    ac_march<R, NF, ADJ, RR, ZC, kMarchAhead, ST, true, MW><<<grid, block, 0, st>>>(a);
   else
-    ac_march<R, NF, ADJ, RR, kMarchPlanes, kMarchAhead, ST, false, MW><<<grid, block, 0, st>>>(a);
+    ac_march<R, NF, ADJ, RR, ZC, kMarchAhead, ST, false, MW><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
 
 // mids (nullable): the intermediate states' buffers, step l's at mids[l-1].
 template <class R, int K, int RPT, int NZ, int BY>
 hipError_t ac_forward_n(const StepShape& s, const R* x, R* y, R* const* mids, hipStream_t st) {
-  using A = AcN<K, RPT, NZ, BY>;
+  using A = AcN<K, RPT, BY>;
   const int tx = cdiv(s.nx, A::OX), ty = cdiv(s.ny, A::OY);
-  const int nt = tx * ty * cdiv(s.nz, A::ZC);
+  const int zc = z_chunk(tx * int64_t(ty), s.nz, NZ, BY == kBY ? kWant4 : kWant16);
+  const int nt = tx * ty * cdiv(s.nz, zc);
   const dim3 grid(xcd_grid(nt)), block(kBX, BY);
   R* m0 = mids ? mids[0] : nullptr;
   R* m1 = (mids && K >= 3) ? mids[1] : nullptr;
   const bool str = streams(s) != 0;
   if (mids && str)
-    fwd_allencahn3d7_n<R, K, RPT, NZ, true, true, BY><<<grid, block, 0, st>>>(
-        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, R(s.p0), R(s.p1));
+    fwd_allencahn3d7_n<R, K, RPT, true, true, BY><<<grid, block, 0, st>>>(
+        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc, R(s.p0), R(s.p1));
   else if (mids)
-    fwd_allencahn3d7_n<R, K, RPT, NZ, false, true, BY><<<grid, block, 0, st>>>(
-        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, R(s.p0), R(s.p1));
+    fwd_allencahn3d7_n<R, K, RPT, false, true, BY><<<grid, block, 0, st>>>(
+        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc, R(s.p0), R(s.p1));
   else if (str)
-    fwd_allencahn3d7_n<R, K, RPT, NZ, true, false, BY><<<grid, block, 0, st>>>(
-        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, R(s.p0), R(s.p1));
+    fwd_allencahn3d7_n<R, K, RPT, true, false, BY><<<grid, block, 0, st>>>(
+        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc, R(s.p0), R(s.p1));
   else
-    fwd_allencahn3d7_n<R, K, RPT, NZ, false, false, BY><<<grid, block, 0, st>>>(
-        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, R(s.p0), R(s.p1));
+    fwd_allencahn3d7_n<R, K, RPT, false, false, BY><<<grid, block, 0, st>>>(
+        x, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc, R(s.p0), R(s.p1));
   return hipGetLastError();
 }
 
@@ -1079,22 +1105,22 @@ hipError_t ac_forward_steps(const StepShape& s, const void* xv, void* yv, void* 
 template <class R>
 hipError_t forward1(const StepShape& s, const R* x, R* y, hipStream_t st) {
   const int tx = cdiv(s.nx, kAcTX), ty = cdiv(s.ny, kAcTY);
-  const int nt = tx * ty * cdiv(s.nz, kAcZC);
+  const int zc = z_chunk(tx * int64_t(ty), s.nz, kAcZC, kWant4), nt = tx * ty * cdiv(s.nz, zc);
   const dim3 grid(xcd_grid(nt)), block(kBX, kBY);
   const bool str = streams(s) != 0;
   const Limit<R> lim{R(s.lo), R(s.hi)};
   if (s.limit && str)
-    fwd_allencahn3d7<R, true, true><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt,
+    fwd_allencahn3d7<R, true, true><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt, zc,
                                                             R(s.p0), R(s.p1), lim);
   else if (s.limit)
-    fwd_allencahn3d7<R, true, false><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt,
+    fwd_allencahn3d7<R, true, false><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt, zc,
                                                              R(s.p0), R(s.p1), lim);
   else if (str)
-    fwd_allencahn3d7<R, false, true><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt,
+    fwd_allencahn3d7<R, false, true><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty, nt, zc,
                                                              R(s.p0), R(s.p1), lim);
   else
     fwd_allencahn3d7<R, false, false><<<grid, block, 0, st>>>(x, y, s.nx, s.ny, s.nz, tx, ty,
-                                                              nt, R(s.p0), R(s.p1), lim);
+                                                              nt, zc, R(s.p0), R(s.p1), lim);
   return hipGetLastError();
 }
 
@@ -1115,15 +1141,16 @@ hipError_t adjoint1(const StepShape& s, const R* x, const R* g, R* gp, double* d
                                                          D, k0, k1, dp)
   // waves (and rows per half-tile) of the limiter's adjoint: 64 x 16 tiles
   // (0.703 -> 0.686 ms per 512^3 step against 64 x 8; 64 x 32 was slower),
-  // marching over 256-plane chunks (0.686 -> 0.620 ms against 32 planes;
+  // marching over chunks of up to 256 planes (0.686 -> 0.620 ms against 32 planes;
   // 128: 0.636). The other tiled kernels keep 32: at 128 the forward with
   // the limiter went from 0.409 to 0.436 ms and the adjoint with the
   // constants' partials from 0.629 to 0.653.
   constexpr int kLimTW = 8, kLimZC = 256;
-  const int tyl = cdiv(s.ny, 2 * kLimTW), ntl = tx * tyl * cdiv(s.nz, kLimZC);
+  const int tyl = cdiv(s.ny, 2 * kLimTW);
+  const int zcl = z_chunk(tx * int64_t(tyl), s.nz, kLimZC, kWantLim), ntl = tx * tyl * cdiv(s.nz, zcl);
 #define ADST_AC_LIM(NTV)                                                                          \
-  adj_allencahn3d7_lim<R, NTV, kLimTW, kLimZC><<<dim3(xcd_grid(ntl)), dim3(kBX, kLimTW), 0, st>>>( \
-      x, g, gp, s.nx, s.ny, s.nz, tx, tyl, ntl, D, k0, k1, C, lim)
+  adj_allencahn3d7_lim<R, NTV, kLimTW><<<dim3(xcd_grid(ntl)), dim3(kBX, kLimTW), 0, st>>>( \
+      x, g, gp, s.nx, s.ny, s.nz, tx, tyl, ntl, zcl, D, k0, k1, C, lim)
   if (dp_part && str)
     ADST_AC_ADJ(true, true);
   else if (dp_part)
