@@ -171,12 +171,62 @@ inline bool make_grid(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int
   return *blocks > 0 && *blocks <= INT32_MAX;
 }
 
+// The V elements from column c0 (a multiple of V) of the row at src, by one
+// 16-byte load clamped into the row. VEC: nx is a multiple of V and rows
+// are 16-byte aligned, so a block is in the grid or outside it; else the load
+// is at element alignment, and the block that holds the row's end is loaded
+// from column nx - V and its elements moved to their places. INNER: c0 .. c0 + V - 1 lie in the grid. With one load per
+// element in such rows, the waves waited on four times as many (a 2501 x 3003
+// f32 call of 60 steps with dL/dw: 4.21 -> 3.51 ms). NT: the non-temporal hint.
+template <class R, bool VEC, bool INNER, bool NT>
+__device__ inline void load_block(const R* src, int c0, int nx, R* out) {
+  constexpr int V = 16 / sizeof(R);
+  typedef R vec_t __attribute__((ext_vector_type(V), aligned(VEC ? 16 : sizeof(R))));
+  if (!VEC && !INNER && nx < V) {  // no whole block in a row (uniform)
+#pragma unroll
+    for (int e = 0; e < V; ++e) out[e] = src[min(max(c0 + e, 0), nx - 1)];
+    return;
+  }
+  const int cc = INNER && !VEC ? c0 : min(max(c0, 0), nx - V);
+  const vec_t* p = reinterpret_cast<const vec_t*>(src + cc);
+  vec_t t;
+  if constexpr (NT)
+    t = __builtin_nontemporal_load(p);
+  else
+    t = *p;
+#pragma unroll
+  for (int e = 0; e < V; ++e) out[e] = t[e];
+  if constexpr (!VEC && !INNER) {
+    const int sh = c0 - cc;  // 1 .. V-1 in the block that holds the row's end
+#pragma unroll
+    for (int d = 1; d < V; d *= 2)
+#pragma unroll
+      for (int e = 0; e + d < V; ++e) out[e] = (sh > 0 && (sh & d)) ? out[e + d] : out[e];
+  }
+}
+
+// Stores the block's elements that lie in the row at dst.
+template <class R, bool VEC>
+__device__ inline void store_block(R* dst, int c0, int nx, const R* o) {
+  constexpr int V = 16 / sizeof(R);
+  typedef R vec_t __attribute__((ext_vector_type(V), aligned(VEC ? 16 : sizeof(R))));
+  if (c0 + V <= nx) {
+    vec_t t;
+#pragma unroll
+    for (int e = 0; e < V; ++e) t[e] = o[e];
+    *reinterpret_cast<vec_t*>(dst + c0) = t;
+  } else if constexpr (!VEC) {
+#pragma unroll
+    for (int e = 0; e < V; ++e)
+      if (c0 + e < nx) dst[c0 + e] = o[e];
+  }
+}
+
 template <class R, int K, bool ADJ, bool VEC>
 __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, R* __restrict__ y,
                                                        int nx, int ny, MarchGrid g, R w) {
   using G = Geom<R, K>;
   constexpr int V = G::V, H = G::H, OW = G::OW, P = kAhead, U = kUnroll;
-  typedef R vec_t __attribute__((ext_vector_type(V)));
   int strip, chunk, r0, r1;
   if (!march_item(g, ny, &strip, &chunk, &r0, &r1)) return;
   const int lane = threadIdx.x;
@@ -210,19 +260,11 @@ __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, 
     }
 
   // Raw load of input row `row` (clamped to the rows the chunk needs, and
-  // to the grid, so every address is in bounds); masked on entry.
-  auto load = [&](int row, R* out) {
+  // to the grid, so every address is in bounds); masked on entry. INNER: all
+  // the strip's columns lie in the grid.
+  auto load = [&](int row, R* out, auto inner_t) {
     const int rr = min(max(row, lo_need), hi_need);
-    const R* src = x + (int64_t)rr * nx;
-    if constexpr (VEC) {
-      const int cc = min(max(c0, 0), nx - V);
-      const vec_t t = *reinterpret_cast<const vec_t*>(src + cc);
-#pragma unroll
-      for (int e = 0; e < V; ++e) out[e] = t[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < V; ++e) out[e] = src[min(max(c0 + e, 0), nx - 1)];
-    }
+    load_block<R, VEC, decltype(inner_t)::value, false>(x + (int64_t)rr * nx, c0, nx, out);
   };
 
   // The adjoint's pipeline holds gi: every ring cell and every cell outside
@@ -250,6 +292,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, 
     R lv[K][3][V];
     R pf[P][V];
     R ring_lo[V], ring_hi[V];
+    constexpr auto inner = std::bool_constant<decltype(mid_t)::value == kFast>{};
 #pragma unroll
     for (int e = 0; e < V; ++e) ring_lo[e] = ring_hi[e] = R(0);
 #pragma unroll
@@ -259,7 +302,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, 
 #pragma unroll
         for (int e = 0; e < V; ++e) lv[k][s3][e] = R(0);
 #pragma unroll
-    for (int u = 0; u < P; ++u) load(ifirst + DIR * u, pf[u]);
+    for (int u = 0; u < P; ++u) load(ifirst + DIR * u, pf[u], inner);
 
     // kFast: rows in [2, ny-3], strip in columns [2, nx-3]: unmasked forms.
     // kCols: rows in [2, ny-3], strip touching the side edges.
@@ -292,7 +335,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, 
 #pragma unroll
             for (int e = 0; e < V; ++e) lv[0][u % 3][e] = (rin && cI[e]) ? pf[u % P][e] : R(0);
           }
-          load(row + DIR * P, pf[u % P]);
+          load(row + DIR * P, pf[u % P], inner);
         }
 #pragma unroll
         for (int k = 1; k <= K; ++k) {
@@ -363,19 +406,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_march(const R* __restrict__ x, 
               for (int e = 0; e < V; ++e)
                 o[e] = j == 0 ? ring_lo[e] : (j == ny - 1 ? ring_hi[e] : o[e]);
             }
-            R* dst = y + (int64_t)j * nx;
-            if constexpr (VEC) {
-              if (c0 + V <= nx) {
-                vec_t t;
-#pragma unroll
-                for (int e = 0; e < V; ++e) t[e] = o[e];
-                *reinterpret_cast<vec_t*>(dst + c0) = t;
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < V; ++e)
-                if (c0 + e < nx) dst[c0 + e] = o[e];
-            }
+            store_block<R, VEC>(y + (int64_t)j * nx, c0, nx, o);
           }
         }
       }
@@ -487,7 +518,6 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
   constexpr int V = 16 / sizeof(R), H = V, OW = kLanes * V - 2 * H, P = 6, U = kUnroll;
   static_assert(H >= 2, "the mask reaches two columns beyond an output");
   static_assert(U % P == 0, "register slots must stay static");
-  typedef R vec_t __attribute__((ext_vector_type(V)));
   int strip, chunk, r0, r1, item;
   if (!march_item(grid, ny, &strip, &chunk, &r0, &r1, &item)) return;
   const int lane = threadIdx.x;
@@ -510,18 +540,9 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
   const bool st_lane = lane * V >= H && lane * V < H + OW;
   // x and g are read once per step, with the non-temporal hint (4096^2
   // f64: 90.5 -> 83.5 us per step; the hint on x alone did nothing)
-  auto load = [&](const R* a, int row, R* out) {
+  auto load = [&](const R* a, int row, R* out, auto inner_t) {
     const int rr = min(max(row, lo_need), hi_need);
-    const R* src = a + (int64_t)rr * nx;
-    if constexpr (VEC) {
-      const int cc = min(max(c0, 0), nx - V);
-      const vec_t t = __builtin_nontemporal_load(reinterpret_cast<const vec_t*>(src + cc));
-#pragma unroll
-      for (int e = 0; e < V; ++e) out[e] = t[e];
-    } else {
-#pragma unroll
-      for (int e = 0; e < V; ++e) out[e] = src[min(max(c0 + e, 0), nx - 1)];
-    }
+    load_block<R, VEC, decltype(inner_t)::value, true>(a + (int64_t)rr * nx, c0, nx, out);
   };
   enum { kFast = 0, kGeneral = 2 };
   auto march = [&](auto dir_t, auto mid_t) {
@@ -530,14 +551,15 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
     // slot p mod 3 holds pipeline index p (row ifirst + DIR*p)
     R xw[3][V], gr[3][V], mg[3][V];
     R px[P][V], pg[P][V];
+    constexpr auto inner = std::bool_constant<decltype(mid_t)::value == kFast>{};
 #pragma unroll
     for (int s3 = 0; s3 < 3; ++s3)
 #pragma unroll
       for (int e = 0; e < V; ++e) xw[s3][e] = gr[s3][e] = mg[s3][e] = R(0);
 #pragma unroll
     for (int u = 0; u < P; ++u) {
-      load(x, ifirst + DIR * u, px[u]);
-      load(g, ifirst + DIR * u, pg[u]);
+      load(x, ifirst + DIR * u, px[u], inner);
+      load(g, ifirst + DIR * u, pg[u], inner);
     }
     auto block = [&](int base, auto mode_t) {
       constexpr int MODE = decltype(mode_t)::value;
@@ -553,8 +575,8 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
             xw[u % 3][e] = ok ? px[u % P][e] : R(0);
             gr[u % 3][e] = ok ? pg[u % P][e] : R(0);
           }
-          load(x, row + DIR * P, px[u % P]);
-          load(g, row + DIR * P, pg[u % P]);
+          load(x, row + DIR * P, px[u % P], inner);
+          load(g, row + DIR * P, pg[u % P], inner);
         }
         {  // mask row index rr-1 from x rows rr-2 .. rr
           const int m = ifirst + DIR * (rr - 1);
@@ -607,19 +629,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
             }
           }
           if (j >= r0 && j < r1 && st_lane) {
-            R* dst = gp + (int64_t)j * nx;
-            if constexpr (VEC) {
-              if (c0 + V <= nx) {
-                vec_t t;
-#pragma unroll
-                for (int e = 0; e < V; ++e) t[e] = o[e];
-                *reinterpret_cast<vec_t*>(dst + c0) = t;
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < V; ++e)
-                if (c0 + e < nx) dst[c0 + e] = o[e];
-            }
+            store_block<R, VEC>(gp + (int64_t)j * nx, c0, nx, o);
           }
         }
       }

@@ -30,19 +30,20 @@ namespace {
 // ------------------------------------------------------- 2-D LDS tiles
 // A workgroup owns a tile of the output: one thread per column, several
 // rows each. It first stages the tile's input rows and columns, plus a halo,
-// in LDS with all loads in flight at once (16-byte vector loads when rows are
-// 16-byte aligned), then computes from LDS. Cells outside the grid read 0;
+// in LDS with all loads in flight at once (16-byte vector loads, which need
+// no alignment beyond the element's), then computes from LDS. Cells outside the grid read 0;
 // no formula evaluated at an in-grid point uses them.
 
 // Stage LR x LW elements of a, starting at global row row0 and column col0
 // (col0 a multiple of the vector width), into lds (row stride LW).
 template <class R, int NT, int LR, int LW>
 __device__ inline void stage_rows(R* lds, const R* __restrict__ a, int col0, int row0, int nx,
-                                  int ny, bool vec) {
+                                  int ny) {
   constexpr int V = 16 / sizeof(R);
   constexpr int CH = LW / V;
   static_assert(LW % V == 0, "LDS rows hold whole 16-byte chunks");
-  typedef R vec_t __attribute__((ext_vector_type(V)));
+  // element-aligned: the memory takes 16-byte loads at any element
+  typedef R vec_t __attribute__((ext_vector_type(V), aligned(sizeof(R))));
   for (int q = threadIdx.x; q < LR * CH; q += NT) {
     const int rr = q / CH, ch = q - rr * CH;
     const int jj = row0 + rr;
@@ -51,7 +52,7 @@ __device__ inline void stage_rows(R* lds, const R* __restrict__ a, int col0, int
     if (jj < 0 || jj >= ny) {
 #pragma unroll
       for (int e = 0; e < V; ++e) dst[e] = R(0);
-    } else if (vec && ii >= 0 && ii + V <= nx) {
+    } else if (ii >= 0 && ii + V <= nx) {
       const vec_t v = *reinterpret_cast<const vec_t*>(a + jj * nx + ii);
 #pragma unroll
       for (int e = 0; e < V; ++e) dst[e] = v[e];
@@ -189,14 +190,14 @@ __device__ inline bool jacobi_all_avg(int ia, int ib, int ja, int jb, int nx, in
 // LIM clamps the forward's new values.
 template <class R, bool ADJ, bool LIM = false>
 __device__ inline void jacobi_tile(const R* __restrict__ x, R* __restrict__ y, int nx, int ny,
-                                   int tiles_x, int ntiles, int vec, R w, Limit<R> lim = {}) {
+                                   int tiles_x, int ntiles, R w, Limit<R> lim = {}) {
   auto out = [&](R v) { return LIM ? limited(v, lim) : v; };
   using G = Tile2<R, kJacTW, kJacTR>;
   __shared__ R s[G::LR * G::LW];
   const int b = xcd_tile(ntiles);
   if (b >= ntiles) return;
   const int i0 = (b % tiles_x) * kJacTW, j0 = (b / tiles_x) * kJacTR;
-  stage_rows<R, kJacTW, G::LR, G::LW>(s, x, i0 - G::V, j0 - 1, nx, ny, vec);
+  stage_rows<R, kJacTW, G::LR, G::LW>(s, x, i0 - G::V, j0 - 1, nx, ny);
   __syncthreads();
   const int i = i0 + (int)threadIdx.x;
   if (i >= nx) return;
@@ -220,13 +221,13 @@ __device__ inline void jacobi_tile(const R* __restrict__ x, R* __restrict__ y, i
 // Two Jacobi steps (forward or adjoint) on one tile in one launch.
 template <class R, bool ADJ>
 __device__ inline void jacobi_tile_x2(const R* __restrict__ x, R* __restrict__ y, int nx, int ny,
-                                      int tiles_x, int ntiles, int vec, R w) {
+                                      int tiles_x, int ntiles, R w) {
   using G = Tile2x2<R, kX2TR>;
   __shared__ R s[G::LR * G::LW];
   const int b = xcd_tile(ntiles);
   if (b >= ntiles) return;
   const int i0 = (b % tiles_x) * kX2TW, j0 = (b / tiles_x) * kX2TR;
-  stage_rows<R, kX2Threads, G::LR, G::LW>(s, x, i0 - G::PADL, j0 - 2, nx, ny, vec);
+  stage_rows<R, kX2Threads, G::LR, G::LW>(s, x, i0 - G::PADL, j0 - 2, nx, ny);
   // the first step covers the tile plus one cell; whole tiles away from the
   // edges take the plain average everywhere (workgroup-uniform)
   const bool avg = jacobi_all_avg<ADJ>(i0 - 1, i0 + kX2TW, j0 - 1, j0 + kX2TR, nx, ny);
@@ -281,29 +282,29 @@ __device__ inline void jacobi_tile_x2(const R* __restrict__ x, R* __restrict__ y
 template <class R, bool LIM>
 __global__ __launch_bounds__(kJacTW) void fwd_jacobi2d5(const R* __restrict__ x,
                                                         R* __restrict__ y, int nx, int ny,
-                                                        int tiles_x, int ntiles, int vec, R w,
+                                                        int tiles_x, int ntiles, R w,
                                                         Limit<R> lim) {
-  jacobi_tile<R, false, LIM>(x, y, nx, ny, tiles_x, ntiles, vec, w, lim);
+  jacobi_tile<R, false, LIM>(x, y, nx, ny, tiles_x, ntiles, w, lim);
 }
 template <class R>
 __global__ __launch_bounds__(kJacTW) void adj_jacobi2d5(const R* __restrict__ g,
                                                         R* __restrict__ gp, int nx, int ny,
-                                                        int tiles_x, int ntiles, int vec, R w) {
-  jacobi_tile<R, true>(g, gp, nx, ny, tiles_x, ntiles, vec, w);
+                                                        int tiles_x, int ntiles, R w) {
+  jacobi_tile<R, true>(g, gp, nx, ny, tiles_x, ntiles, w);
 }
 template <class R>
 __global__ __launch_bounds__(kX2Threads) void fwd_jacobi2d5_x2(const R* __restrict__ x,
                                                                R* __restrict__ y, int nx, int ny,
-                                                               int tiles_x, int ntiles, int vec,
+                                                               int tiles_x, int ntiles,
                                                                R w) {
-  jacobi_tile_x2<R, false>(x, y, nx, ny, tiles_x, ntiles, vec, w);
+  jacobi_tile_x2<R, false>(x, y, nx, ny, tiles_x, ntiles, w);
 }
 template <class R>
 __global__ __launch_bounds__(kX2Threads) void adj_jacobi2d5_x2(const R* __restrict__ g,
                                                                R* __restrict__ gp, int nx, int ny,
-                                                               int tiles_x, int ntiles, int vec,
+                                                               int tiles_x, int ntiles,
                                                                R w) {
-  jacobi_tile_x2<R, true>(g, gp, nx, ny, tiles_x, ntiles, vec, w);
+  jacobi_tile_x2<R, true>(g, gp, nx, ny, tiles_x, ntiles, w);
 }
 
 // ------------------------------------------ variable-coefficient diffusion 2-D
@@ -313,7 +314,7 @@ template <class R, bool LIM, bool NT>
 __global__ __launch_bounds__(kVdTW) void fwd_vardiff2d9(const R* __restrict__ x,
                                                         const R* __restrict__ K,
                                                         R* __restrict__ y, int nx, int ny,
-                                                        int tiles_x, int ntiles, int vec, R dt,
+                                                        int tiles_x, int ntiles, R dt,
                                                         R ca, R cd, Limit<R> lim) {
   using G = Tile2<R, kVdTW, kVdTR>;
   __shared__ R sx[G::LR * G::LW];
@@ -321,8 +322,8 @@ __global__ __launch_bounds__(kVdTW) void fwd_vardiff2d9(const R* __restrict__ x,
   const int b = xcd_tile(ntiles);
   if (b >= ntiles) return;
   const int i0 = (b % tiles_x) * kVdTW, j0 = (b / tiles_x) * kVdTR;
-  stage_rows<R, kVdTW, G::LR, G::LW>(sx, x, i0 - G::V, j0 - 1, nx, ny, vec);
-  stage_rows<R, kVdTW, G::LR, G::LW>(sk, K, i0 - G::V, j0 - 1, nx, ny, vec);
+  stage_rows<R, kVdTW, G::LR, G::LW>(sx, x, i0 - G::V, j0 - 1, nx, ny);
+  stage_rows<R, kVdTW, G::LR, G::LW>(sk, K, i0 - G::V, j0 - 1, nx, ny);
   __syncthreads();
   const int i = i0 + (int)threadIdx.x;
   if (i >= nx) return;
@@ -398,7 +399,7 @@ __global__ __launch_bounds__(kX2Threads) void fwd_vardiff2d9_x2(const R* __restr
                                                                 R* __restrict__ y,
                                                                 R* __restrict__ mid, int nx,
                                                                 int ny, int tiles_x, int ntiles,
-                                                                int vec, R dt, R ca, R cd) {
+                                                                R dt, R ca, R cd) {
   using G = Tile2x2<R, TR>;
   __shared__ R sx[G::LR * G::LW];
   __shared__ R sk[G::LR * G::LW];
@@ -406,8 +407,8 @@ __global__ __launch_bounds__(kX2Threads) void fwd_vardiff2d9_x2(const R* __restr
   if (b >= ntiles) return;
   const int i0 = (b % tiles_x) * kX2TW, j0 = (b / tiles_x) * TR;
   // LDS row r is grid row j0 - 2 + r, LDS column c grid column i0 - PADL + c
-  stage_rows<R, kX2Threads, G::LR, G::LW>(sx, x, i0 - G::PADL, j0 - 2, nx, ny, vec);
-  stage_rows<R, kX2Threads, G::LR, G::LW>(sk, K, i0 - G::PADL, j0 - 2, nx, ny, vec);
+  stage_rows<R, kX2Threads, G::LR, G::LW>(sx, x, i0 - G::PADL, j0 - 2, nx, ny);
+  stage_rows<R, kX2Threads, G::LR, G::LW>(sk, K, i0 - G::PADL, j0 - 2, nx, ny);
   __syncthreads();
   const int t = threadIdx.x;
   R xw[3][3], kw[3][3];
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(kVdTW) void adj_vardiff2d9(const R* __restrict__ x,
                                                         const R* __restrict__ g,
                                                         R* __restrict__ gp, R* __restrict__ dK,
                                                         int dk_first, int nx, int ny,
-                                                        int tiles_x, int ntiles, int vec, R dt,
+                                                        int tiles_x, int ntiles, R dt,
                                                         R ca, R cd, DpOut dp) {
   constexpr bool XS = WANT_DK || DP;  // x_{t-1} staged
   using G = Tile2<R, kVdTW, TR>;
@@ -517,9 +518,9 @@ __global__ __launch_bounds__(kVdTW) void adj_vardiff2d9(const R* __restrict__ x,
   const int i0 = (b % tiles_x) * kVdTW, j0 = (b / tiles_x) * TR;
   DpPrev prev;
   if (DP) prev = dp_prev<1>(dp, b);
-  stage_rows<R, kVdTW, G::LR, LW>(sg, g, i0 - G::V, j0 - 1, nx, ny, vec);
-  stage_rows<R, kVdTW, G::LR, LW>(sk, K, i0 - G::V, j0 - 1, nx, ny, vec);
-  if (XS) stage_rows<R, kVdTW, G::LR, LW>(sx, x, i0 - G::V, j0 - 1, nx, ny, vec);
+  stage_rows<R, kVdTW, G::LR, LW>(sg, g, i0 - G::V, j0 - 1, nx, ny);
+  stage_rows<R, kVdTW, G::LR, LW>(sk, K, i0 - G::V, j0 - 1, nx, ny);
+  if (XS) stage_rows<R, kVdTW, G::LR, LW>(sx, x, i0 - G::V, j0 - 1, nx, ny);
   const int i = i0 + (int)threadIdx.x;
   // the accumulated dK of the thread's cells, requested with the staged
   // rows (the row loop is unrolled, so the registers stay static)
@@ -742,16 +743,6 @@ int grid_for(int64_t n, int64_t per_block, int64_t cap) {
   return (int)b;
 }
 
-// 16-byte vector loads need every staged array 16-byte aligned and rows whose
-// starts stay aligned (nx a multiple of the vector width).
-template <class R>
-int vec_ok(int nx, const void* a, const void* b = nullptr, const void* c = nullptr) {
-  if (nx % (16 / (int)sizeof(R))) return 0;
-  for (const void* p : {a, b, c})
-    if (p && (reinterpret_cast<uintptr_t>(p) & 15u)) return 0;
-  return 1;
-}
-
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // 1 when the kernels of this shape stream their stores (see kStreamBytes)
@@ -774,15 +765,15 @@ hipError_t forward_t(const StepShape& s, const void* xv, const void* Kv, void* y
       if (two) {
         const int tx = cdiv(s.nx, kX2TW), nt = tx * cdiv(s.ny, kX2TR);
         fwd_jacobi2d5_x2<R><<<dim3(xcd_grid(nt)), dim3(kX2Threads), 0, st>>>(
-            x, y, s.nx, s.ny, tx, nt, vec_ok<R>(s.nx, x), R(s.p0));
+            x, y, s.nx, s.ny, tx, nt, R(s.p0));
       } else {
         const int tx = cdiv(s.nx, kJacTW), nt = tx * cdiv(s.ny, kJacTR);
         if (s.limit)
           fwd_jacobi2d5<R, true><<<dim3(xcd_grid(nt)), dim3(kJacTW), 0, st>>>(
-              x, y, s.nx, s.ny, tx, nt, vec_ok<R>(s.nx, x), R(s.p0), lim);
+              x, y, s.nx, s.ny, tx, nt, R(s.p0), lim);
         else
           fwd_jacobi2d5<R, false><<<dim3(xcd_grid(nt)), dim3(kJacTW), 0, st>>>(
-              x, y, s.nx, s.ny, tx, nt, vec_ok<R>(s.nx, x), R(s.p0), lim);
+              x, y, s.nx, s.ny, tx, nt, R(s.p0), lim);
       }
       break;
     }
@@ -791,39 +782,34 @@ hipError_t forward_t(const StepShape& s, const void* xv, const void* Kv, void* y
                  : ac_launch_forward(s, x, y, st);
     case ADST_VARDIFF2D9: {
       const bool str = streams(s) != 0;
-      const int vec = vec_ok<R>(s.nx, x, K);
       const R dt = R(s.p0), ca = R(1) / R(3), cd = R(1) / R(12);
       if (two) {
         const int tx = cdiv(s.nx, kX2TW), nt = tx * cdiv(s.ny, kVdX2TR);
         const dim3 grid(xcd_grid(nt)), block(kX2Threads);
         if (mid && str)
           fwd_vardiff2d9_x2<R, kVdX2TR, true, true><<<grid, block, 0, st>>>(
-              x, K, y, mid, s.nx, s.ny, tx, nt, vec, dt, ca, cd);
+              x, K, y, mid, s.nx, s.ny, tx, nt, dt, ca, cd);
         else if (mid)
           fwd_vardiff2d9_x2<R, kVdX2TR, false, true><<<grid, block, 0, st>>>(
-              x, K, y, mid, s.nx, s.ny, tx, nt, vec, dt, ca, cd);
+              x, K, y, mid, s.nx, s.ny, tx, nt, dt, ca, cd);
         else if (str)
           fwd_vardiff2d9_x2<R, kVdX2TR, true, false><<<grid, block, 0, st>>>(
-              x, K, y, mid, s.nx, s.ny, tx, nt, vec, dt, ca, cd);
+              x, K, y, mid, s.nx, s.ny, tx, nt, dt, ca, cd);
         else
           fwd_vardiff2d9_x2<R, kVdX2TR, false, false><<<grid, block, 0, st>>>(
-              x, K, y, mid, s.nx, s.ny, tx, nt, vec, dt, ca, cd);
+              x, K, y, mid, s.nx, s.ny, tx, nt, dt, ca, cd);
         break;
       }
       const int tx = cdiv(s.nx, kVdTW), nt = tx * cdiv(s.ny, kVdTR);
       const dim3 grid(xcd_grid(nt)), block(kVdTW);
       if (s.limit && str)
-        fwd_vardiff2d9<R, true, true><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, vec,
-                                                              dt, ca, cd, lim);
+        fwd_vardiff2d9<R, true, true><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, dt, ca, cd, lim);
       else if (s.limit)
-        fwd_vardiff2d9<R, true, false><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, vec,
-                                                               dt, ca, cd, lim);
+        fwd_vardiff2d9<R, true, false><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, dt, ca, cd, lim);
       else if (str)
-        fwd_vardiff2d9<R, false, true><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, vec,
-                                                               dt, ca, cd, lim);
+        fwd_vardiff2d9<R, false, true><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, dt, ca, cd, lim);
       else
-        fwd_vardiff2d9<R, false, false><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, vec,
-                                                                dt, ca, cd, lim);
+        fwd_vardiff2d9<R, false, false><<<grid, block, 0, st>>>(x, K, y, s.nx, s.ny, tx, nt, dt, ca, cd, lim);
       break;
     }
     default:
@@ -835,15 +821,15 @@ hipError_t forward_t(const StepShape& s, const void* xv, const void* Kv, void* y
 // One variable-coefficient adjoint launch over ntiles tiles, streaming or not.
 template <class R, bool WANT_DK, int TR, bool DP>
 void vd_adjoint(bool str, int ntiles, hipStream_t st, const R* x, const R* K, const R* g, R* gp,
-                R* dK, int dk_first, int nx, int ny, int tiles_x, int vec, R dt, R ca, R cd,
+                R* dK, int dk_first, int nx, int ny, int tiles_x, R dt, R ca, R cd,
                 DpOut dp) {
   const dim3 grid(xcd_grid(ntiles)), block(kVdTW);
   if (str)
     adj_vardiff2d9<R, WANT_DK, TR, DP, true><<<grid, block, 0, st>>>(
-        x, K, g, gp, dK, dk_first, nx, ny, tiles_x, ntiles, vec, dt, ca, cd, dp);
+        x, K, g, gp, dK, dk_first, nx, ny, tiles_x, ntiles, dt, ca, cd, dp);
   else
     adj_vardiff2d9<R, WANT_DK, TR, DP, false><<<grid, block, 0, st>>>(
-        x, K, g, gp, dK, dk_first, nx, ny, tiles_x, ntiles, vec, dt, ca, cd, dp);
+        x, K, g, gp, dK, dk_first, nx, ny, tiles_x, ntiles, dt, ca, cd, dp);
 }
 
 template <class R>
@@ -869,7 +855,7 @@ hipError_t adjoint_t(const StepShape& s, const void* xv, const void* Kv, const v
         return launch_jacobi_dp_adjoint(s, xv, gv, gpv, dp_part, dp_first, st);
       }
       adj_jacobi2d5<R><<<dim3(xcd_grid(nt)), dim3(kJacTW), 0, st>>>(
-          g, gp, s.nx, s.ny, tx, nt, vec_ok<R>(s.nx, g), R(s.p0));
+          g, gp, s.nx, s.ny, tx, nt, R(s.p0));
       break;
     }
     case ADST_ALLENCAHN3D7:
@@ -879,20 +865,17 @@ hipError_t adjoint_t(const StepShape& s, const void* xv, const void* Kv, const v
       const R dt = R(s.p0), ca = R(1) / R(3), cd = R(1) / R(12);
       const int nt4 = tx * cdiv(s.ny, kVdAdjTR);
       const bool str = streams(s) != 0;
-      const int dkf = dk_first ? 1 : 0, vx = vec_ok<R>(s.nx, g, K, x);
+      const int dkf = dk_first ? 1 : 0;
       if (dK && dp_part)
-        vd_adjoint<R, true, kVdAdjTR, true>(str, nt4, st, x, K, g, gp, dK, dkf, s.nx, s.ny, tx,
-                                            vx, dt, ca, cd, dp);
+        vd_adjoint<R, true, kVdAdjTR, true>(str, nt4, st, x, K, g, gp, dK, dkf, s.nx, s.ny, tx, dt, ca, cd, dp);
       else if (dK)
-        vd_adjoint<R, true, kVdAdjTR, false>(str, nt4, st, x, K, g, gp, dK, dkf, s.nx, s.ny, tx,
-                                             vx, dt, ca, cd, dp);
+        vd_adjoint<R, true, kVdAdjTR, false>(str, nt4, st, x, K, g, gp, dK, dkf, s.nx, s.ny, tx, dt, ca, cd, dp);
       else if (dp_part)
         vd_adjoint<R, false, kVdAdjTR, true>(str, nt4, st, x, K, g, gp, nullptr, 0, s.nx, s.ny,
-                                             tx, vx, dt, ca, cd, dp);
+                                             tx, dt, ca, cd, dp);
       else
         vd_adjoint<R, false, kVdTR, false>(str, tx * cdiv(s.ny, kVdTR), st, nullptr, K, g, gp,
-                                           nullptr, 0, s.nx, s.ny, tx, vec_ok<R>(s.nx, g, K), dt,
-                                           ca, cd, dp);
+                                           nullptr, 0, s.nx, s.ny, tx, dt, ca, cd, dp);
       break;
     }
     default:
@@ -908,7 +891,7 @@ hipError_t adjoint2_t(const StepShape& s, const void* gv, void* gpv, hipStream_t
   if (s.kind != ADST_JACOBI2D5) return hipErrorInvalidValue;
   const int tx = cdiv(s.nx, kX2TW), nt = tx * cdiv(s.ny, kX2TR);
   adj_jacobi2d5_x2<R><<<dim3(xcd_grid(nt)), dim3(kX2Threads), 0, st>>>(
-      g, gp, s.nx, s.ny, tx, nt, vec_ok<R>(s.nx, g), R(s.p0));
+      g, gp, s.nx, s.ny, tx, nt, R(s.p0));
   return hipGetLastError();
 }
 
