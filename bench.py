@@ -144,7 +144,9 @@ def median_ci95(xs):
 # ------------------------------------------------------------ source hashes
 def kernel_source(kernel):
     """The source file holding a kernel (by its library label)."""
-    if kernel.startswith("jacobi_march") or kernel.startswith("jacobi_lim_adjoint"):
+    if kernel.startswith("jacobi_march"):
+        return "jacobi_march.h"
+    if kernel.startswith("jacobi_lim_adjoint"):
         return "jacobi_march.hip"
     if kernel.startswith("gs_wave"):
         return "gauss_seidel.hip"
@@ -515,8 +517,10 @@ def rocprof_label(name):
         return f"fwd_allencahn3d7_n<{targs[1]}" + (",store>" if t(5) else ">")
     if base == "fwd_vardiff2d9_x2":    # <R, TR, NT, ST>
         return "fwd_vardiff2d9_x2" + ("<store>" if t(3) else "")
-    if base == "jacobi_march":         # <R, K, ADJ, VEC>
-        return f"jacobi_march<{'adj' if t(2) else 'fwd'},{targs[1]}>"
+    if base == "jacobi_march":         # <R, K, ADJ, VEC, LIM, ST, ...>
+        return (f"jacobi_march<{'adj' if t(2) else 'fwd'},{targs[1]}" +
+                (",lim" if len(targs) > 4 and t(4) else "") +
+                (",store>" if len(targs) > 5 and t(5) else ">"))
     if base == "jacobi_lim_adjoint":   # <R, VEC, DP>
         return "jacobi_lim_adjoint<dp>" if t(2) else "jacobi_lim_adjoint"
     if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>

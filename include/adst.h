@@ -132,8 +132,8 @@ typedef enum {
                                 where y was kept, 0 where clamped), and the reverse sweep
                                 recomputes each branch outcome from x_{t-1} with the
                                 forward's own expressions, so every adjoint reads state. Not
-                                built for the in-place kind (ADST_ERR_UNSUPPORTED); steps
-                                are then not fused. */
+                                built for the in-place kind (ADST_ERR_UNSUPPORTED); of
+                                the others, only Jacobi forward steps are then fused. */
 
 /* Which gradients besides dx0 a plan is for (the `grads` argument).
  *   ADST_GRAD_COEFF   dK, the per-point coefficient field (VARDIFF2D9 only)
@@ -181,10 +181,11 @@ typedef struct {
  * steps an action covers (1 for FWD/ADJ, 0 for SEED).
  * Consecutive FWD actions that form a chain (each reads the state the one
  * before it wrote, into buffers all different from each other and from the
- * chain's input) are run by adst_vjp as one launch per up to 3 (Allen-Cahn)
- * or 2 (variable coefficients) of them, which writes every state of the run
- * (a store-all run of the binomial schedule); fwd_kernels counts those
- * launches. Not with ADST_NO_FUSE or ADST_LIMIT. */
+ * chain's input) are run by adst_vjp as one launch per up to 4 (Jacobi),
+ * 3 (Allen-Cahn) or 2 (variable coefficients) of them, which writes every
+ * state of the run (a store-all run of the binomial schedule); fwd_kernels
+ * counts those launches. Not with ADST_NO_FUSE, and with ADST_LIMIT only
+ * Jacobi. */
 typedef enum {
   ADST_OP_FWD = 0,
   ADST_OP_SEED = 1,

@@ -106,10 +106,15 @@ adst_status check_problem(const adst_problem* p, int32_t grads, Checked* out) {
   out->want_dp = want_dp;
   out->trace = (p->flags & ADST_TRACE) != 0;
   const bool fuse = (p->flags & ADST_NO_FUSE) == 0;
-  out->fuse_fwd = (fuse && !limit) ? max_fused_forward(p->kind) : 1;
+  // under the limiter only Jacobi has launches of several forward steps
+  const bool fuse_steps = fuse && (!limit || p->kind == ADST_JACOBI2D5);
+  out->fuse_fwd = fuse_steps ? max_fused_forward(p->kind) : 1;
   out->fuse_adj = fuse ? max_fused_adjoint(p->kind, p->n[0]) : 1;
   out->in_place = p->kind == ADST_GAUSSSEIDEL2D5;
-  out->store_fwd = (fuse && !limit) ? max_stored_forward(p->kind) : 1;
+  // Jacobi grids of a few workgroups keep a launch (and its bytes in the plan)
+  // per kept state: there a launch is its latency, not its bytes.
+  const bool store = fuse_steps && (p->kind != ADST_JACOBI2D5 || n >= kJacStorePoints);
+  out->store_fwd = store ? max_stored_forward(p->kind) : 1;
   out->fuse_adj_fwd = fuse && p->kind == ADST_ALLENCAHN3D7 && ac_fuses_forward_adjoint(out->shape);
   // Allen-Cahn: two 2-step launches take less time than a 3-step launch and
   // a single step (at 1024^3 f64: 3.7 + 3.7 against 4.5 + 3.3 ms).
@@ -251,14 +256,16 @@ std::string kernel_label(const Checked& c, const adst_action& a, int32_t stored,
   const bool march = k == ADST_ALLENCAHN3D7 && !c.shape.limit && ac_fuses_forward_adjoint(c.shape);
   if (march && adj && a.n == 1 && !dparams) return "ac_march<adj>";
   if (!adj) {
+    if (k == ADST_JACOBI2D5 && (stored >= 2 || a.n >= 3 || (a.n == 2 && c.shape.limit)))
+      return "jacobi_march<fwd," + std::to_string(stored >= 2 ? stored : a.n) +
+             (c.shape.limit ? ",lim" : "") + (stored >= 2 ? ",store>" : ">");
     if (stored >= 2)
       return k == ADST_ALLENCAHN3D7
                  ? "fwd_allencahn3d7_n<" + std::to_string(stored) + ",store>"
                  : std::string(kFwd[k]) + "_x2<store>";
     if (a.n <= 1) return c.shape.limit ? std::string(kFwd[k]) + "<lim>" : std::string(kFwd[k]);
     if (k == ADST_ALLENCAHN3D7) return "fwd_allencahn3d7_n<" + std::to_string(a.n) + ">";
-    if (a.n == 2) return std::string(kFwd[k]) + "_x2";
-    return "jacobi_march<fwd," + std::to_string(a.n) + ">";
+    return std::string(kFwd[k]) + "_x2";
   }
   if (a.n >= 3) return "jacobi_march<adj," + std::to_string(a.n) + ">";
   if (a.n == 2) return std::string(kAdj[k]) + "_x2";

@@ -56,9 +56,11 @@ hipError_t launch_forward_n(const StepShape& s, const void* x, const void* K, vo
 // A run of n single steps whose every state is kept (2 <= n <=
 // max_stored_forward): x_{t-n+1+k} = F^{k+1}(x_{t-n}) into ys[k] for
 // k = 0 .. n-1, in one launch that reads x once and writes each state once.
-// The ys are distinct and none overlaps x. Allen-Cahn and the
-// variable-coefficient kind only, without the limiter.
-constexpr int32_t kMaxStoredRun = kAcMaxFuse;
+// The ys are distinct and none overlaps x. Not the in-place kind; with the
+// limiter Jacobi only.
+constexpr int32_t kJacMaxStore = 4;
+constexpr int64_t kJacStorePoints = 1024;  // on grids of fewer points, no such runs
+constexpr int32_t kMaxStoredRun = kJacMaxStore > kAcMaxFuse ? kJacMaxStore : kAcMaxFuse;
 int32_t max_stored_forward(int32_t kind);
 hipError_t launch_forward_store(const StepShape& s, const void* x, const void* K, void* const* ys,
                                 int32_t n, hipStream_t stream);
@@ -70,6 +72,14 @@ hipError_t launch_adjoint_n(const StepShape& s, const void* g_next, void* g_prev
 // Jacobi only, 3 <= n <= kJacMaxFuse: n forward steps (adjoint = false) or
 // n adjoint steps in one launch (jacobi_march.hip).
 hipError_t launch_jacobi_march(const StepShape& s, const void* x, void* y, int32_t n, bool adjoint,
+                               hipStream_t stream);
+
+// Jacobi under the limiter, 2 <= n <= kJacMaxFuse forward steps
+// (jacobi_march_lim.hip), and store-through runs of 2 <= n <= kJacMaxStore
+// steps with or without it (jacobi_march_store.hip).
+hipError_t launch_jacobi_march_lim(const StepShape& s, const void* x, void* y, int32_t n,
+                                   hipStream_t stream);
+hipError_t launch_jacobi_store(const StepShape& s, const void* x, void* const* ys, int32_t n,
                                hipStream_t stream);
 
 // Jacobi under the limiter: one adjoint step with the branch mask of step t

@@ -933,6 +933,8 @@ hipError_t launch_forward(const StepShape& s, const void* x, const void* K, void
 
 int32_t max_stored_forward(int32_t kind) {
   switch (kind) {
+    case ADST_JACOBI2D5:
+      return kJacMaxStore;
     case ADST_ALLENCAHN3D7:
       return kAcMaxFuse;
     case ADST_VARDIFF2D9:
@@ -943,7 +945,9 @@ int32_t max_stored_forward(int32_t kind) {
 
 hipError_t launch_forward_store(const StepShape& s, const void* x, const void* K, void* const* ys,
                                 int32_t n, hipStream_t stream) {
-  if (n < 2 || n > max_stored_forward(s.kind) || s.limit) return hipErrorInvalidValue;
+  if (n < 2 || n > max_stored_forward(s.kind)) return hipErrorInvalidValue;
+  if (s.kind == ADST_JACOBI2D5) return launch_jacobi_store(s, x, ys, n, stream);
+  if (s.limit) return hipErrorInvalidValue;
   if (s.kind == ADST_ALLENCAHN3D7) return ac_launch_forward_steps(s, x, ys[n - 1], ys, n, stream);
   return s.dtype == ADST_F64 ? forward_t<double>(s, x, K, ys[1], true, stream, ys[0])
                              : forward_t<float>(s, x, K, ys[1], true, stream, ys[0]);
@@ -970,6 +974,7 @@ int32_t max_fused_adjoint(int32_t kind, int64_t nx) {
 hipError_t launch_forward_n(const StepShape& s, const void* x, const void* K, void* y, int32_t n,
                             hipStream_t stream) {
   if (n < 2 || n > max_fused_forward(s.kind)) return hipErrorInvalidValue;
+  if (s.limit) return launch_jacobi_march_lim(s, x, y, n, stream);  // no other kind
   if (s.kind == ADST_ALLENCAHN3D7) return ac_launch_forward_steps(s, x, y, nullptr, n, stream);
   if (n == 2)
     return s.dtype == ADST_F64 ? forward_t<double>(s, x, K, y, true, stream)
