@@ -148,6 +148,8 @@ def kernel_source(kernel):
         return "jacobi_march.h"
     if kernel.startswith("jacobi_lim_adjoint"):
         return "jacobi_march.hip"
+    if kernel.startswith("vd_march"):
+        return "vardiff_march.hip"
     if kernel.startswith("gs_wave"):
         return "gauss_seidel.hip"
     if kernel.startswith("gs_pipe"):
@@ -521,6 +523,8 @@ def rocprof_label(name):
         return (f"jacobi_march<{'adj' if t(2) else 'fwd'},{targs[1]}" +
                 (",lim" if len(targs) > 4 and t(4) else "") +
                 (",store>" if len(targs) > 5 and t(5) else ">"))
+    if base == "vd_march":             # <R, VEC, ST, NT>
+        return "vd_march<store>" if t(2) else "vd_march"
     if base == "jacobi_lim_adjoint":   # <R, VEC, DP>
         return "jacobi_lim_adjoint<dp>" if t(2) else "jacobi_lim_adjoint"
     if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>

@@ -262,10 +262,10 @@ std::string kernel_label(const Checked& c, const adst_action& a, int32_t stored,
     if (stored >= 2)
       return k == ADST_ALLENCAHN3D7
                  ? "fwd_allencahn3d7_n<" + std::to_string(stored) + ",store>"
-                 : std::string(kFwd[k]) + "_x2<store>";
+                 : "vd_march<store>";
     if (a.n <= 1) return c.shape.limit ? std::string(kFwd[k]) + "<lim>" : std::string(kFwd[k]);
     if (k == ADST_ALLENCAHN3D7) return "fwd_allencahn3d7_n<" + std::to_string(a.n) + ">";
-    return std::string(kFwd[k]) + "_x2";
+    return k == ADST_VARDIFF2D9 ? "vd_march" : std::string(kFwd[k]) + "_x2";
   }
   if (a.n >= 3) return "jacobi_march<adj," + std::to_string(a.n) + ">";
   if (a.n == 2) return std::string(kAdj[k]) + "_x2";

@@ -65,6 +65,11 @@ int32_t max_stored_forward(int32_t kind);
 hipError_t launch_forward_store(const StepShape& s, const void* x, const void* K, void* const* ys,
                                 int32_t n, hipStream_t stream);
 
+// Variable coefficients: two forward steps (vardiff_march.hip); mid
+// (nullable) receives the first one's state.
+hipError_t launch_vardiff_march(const StepShape& s, const void* x, const void* K, void* y,
+                                void* mid, hipStream_t stream);
+
 // g_{t-n} = J_{t-n+1}^T ... J_t^T g_t in one launch, state-free adjoints.
 hipError_t launch_adjoint_n(const StepShape& s, const void* g_next, void* g_prev, int32_t n,
                             hipStream_t stream);
