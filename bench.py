@@ -146,6 +146,8 @@ def kernel_source(kernel):
     """The source file holding a kernel (by its library label)."""
     if kernel.startswith("jacobi_march"):
         return "jacobi_march.h"
+    if kernel.startswith("jacobi_pair_adjoint"):
+        return "jacobi_pair.hip"
     if kernel.startswith("jacobi_lim_adjoint"):
         return "jacobi_march.hip"
     if kernel.startswith("vd_march"):
@@ -525,8 +527,8 @@ def rocprof_label(name):
                 (",store>" if len(targs) > 5 and t(5) else ">"))
     if base == "vd_march":             # <R, VEC, ST, NT>
         return "vd_march<store>" if t(2) else "vd_march"
-    if base == "jacobi_lim_adjoint":   # <R, VEC, DP>
-        return "jacobi_lim_adjoint<dp>" if t(2) else "jacobi_lim_adjoint"
+    if base in ("jacobi_lim_adjoint", "jacobi_pair_adjoint"):  # <R, VEC, DP>
+        return base + ("<dp>" if t(2) else "")
     if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>
         return base + ("<adj>" if t(1) else "<fwd>")
     if base == "ac_march":             # <R, NF, ADJ, RR, ZC, DA, ST, NT>

@@ -20,7 +20,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 
 HOST_SOURCES = ["planner.cpp", "ilp.cpp", "abi.cpp"]
 HIP_SOURCES = ["kernels.hip", "allencahn.hip", "jacobi_march.hip", "jacobi_march_lim.hip",
-               "jacobi_march_store.hip", "gauss_seidel.hip", "gs_pipe.hip",
+               "jacobi_march_store.hip", "jacobi_pair.hip", "gauss_seidel.hip", "gs_pipe.hip",
                "vardiff_march.hip", "static_ws.hip"]
 
 COMMON = ["-std=c++17", "-O3", "-fPIC", "-ffp-contract=off", "-Wall",

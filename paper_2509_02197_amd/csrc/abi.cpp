@@ -51,6 +51,7 @@ struct Checked {
   int32_t store_fwd = 1;  // most single steps per launch that stores every state
   bool fuse_adj_fwd = false;  // a recomputed step may share the adjoint's launch
   bool pair_tail = false;     // build_plan's pair_tail
+  bool pair_adj = false;      // two adjoint steps that read state may share a launch
   bool in_place = false;  // the Gauss-Seidel kind: pipelined sweeps, adjoint in place
   bool want_dk = false, want_dp = false;
 };
@@ -116,6 +117,7 @@ adst_status check_problem(const adst_problem* p, int32_t grads, Checked* out) {
   const bool store = fuse_steps && (p->kind != ADST_JACOBI2D5 || n >= kJacStorePoints);
   out->store_fwd = store ? max_stored_forward(p->kind) : 1;
   out->fuse_adj_fwd = fuse && p->kind == ADST_ALLENCAHN3D7 && ac_fuses_forward_adjoint(out->shape);
+  out->pair_adj = fuse && jacobi_pairs_adjoint(out->shape, want_dp);
   // Allen-Cahn: two 2-step launches take less time than a 3-step launch and
   // a single step (at 1024^3 f64: 3.7 + 3.7 against 4.5 + 3.3 ms).
   out->pair_tail = out->fuse_fwd == 3 && p->kind == ADST_ALLENCAHN3D7;
@@ -169,6 +171,25 @@ int32_t stored_run(const Checked& c, const std::vector<adst_action>& acts, size_
     if (clash) break;
     ++n;
   }
+  return n;
+}
+
+// acts[i] and acts[i + 1] are adjoint steps t and t-1 that share a launch
+// (launch_jacobi_pair_adjoint).
+bool paired_adj(const Checked& c, const std::vector<adst_action>& acts, size_t i) {
+  return c.pair_adj && i + 1 < acts.size() && acts[i].op == ADST_OP_ADJ &&
+         acts[i + 1].op == ADST_OP_ADJ && acts[i].src != ADST_BUF_NONE &&
+         acts[i + 1].src != ADST_BUF_NONE;
+}
+
+// Adjoint launches that write a gradient buffer: the buffers alternate.
+int64_t adjoint_swaps(const Checked& c, const Plan& plan) {
+  int64_t n = plan.adj_launches;
+  for (size_t i = 0; i < plan.acts.size(); ++i)
+    if (paired_adj(c, plan.acts, i)) {
+      --n;
+      ++i;
+    }
   return n;
 }
 
@@ -314,7 +335,7 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
     if (fused_fwd_adj(c, plan.acts, i)) continue;  // counted with its adjoint
     const int64_t k = c.in_place ? gs_kernel_launches(c.shape, adj_op, a.n) : 1;
     (fwd_op ? info->fwd_kernels : info->adj_kernels) += k;
-    i += stored_run(c, plan.acts, i) - 1;
+    i += paired_adj(c, plan.acts, i) ? 1 : stored_run(c, plan.acts, i) - 1;
   }
   info->state_bytes = c.state_bytes;
   info->budget_bytes = budget;
@@ -348,6 +369,10 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
       case ADST_OP_ADJ2:
         per_point += (first_adj ? ab1 : ab) + db;
         first_adj = false;
+        if (paired_adj(c, plan.acts, i)) {  // and the second step's state
+          per_point += itemsize(c.shape.dtype);
+          ++i;
+        }
         break;
       case ADST_OP_ADJW:
         per_point += uint64_t(a.n) * ab;
@@ -643,7 +668,7 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
   double* partials = reinterpret_cast<double*>(wsb);
   double* loss_out = loss_dev ? loss_dev : reinterpret_cast<double*>(wsb + kLossOffset);
   void* gws = wsb + L.g;
-  void* gcur = (c.in_place || plan.adj_launches % 2 == 0) ? dx0 : gws;
+  void* gcur = (c.in_place || adjoint_swaps(c, plan) % 2 == 0) ? dx0 : gws;
   void* gnext = (gcur == dx0) ? gws : dx0;
   void* const g_T = gcur;
   const bool g_T_is_aux = seed_in_aux(c, loss, steps);
@@ -768,6 +793,19 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
         break;
       }
       case ADST_OP_ADJ: {
+        if (paired_adj(c, plan.acts, ai)) {
+          const adst_action& b = plan.acts[ai + 1];
+          const double bytes = npts * double((first_adj ? pp.adj_first : pp.adj) + pp.adj_extra +
+                                             itemsize(c.shape.dtype));
+          e = traced(cat, dparams ? "jacobi_pair_adjoint<dp>" : "jacobi_pair_adjoint", bytes, [&] {
+            return launch_jacobi_pair_adjoint(c.shape, buffer(a.src), buffer(b.src), g_in(), gnext,
+                                              dparams ? dp_part : nullptr, a.t == steps, stream);
+          });
+          std::swap(gcur, gnext);
+          first_adj = false;
+          ++ai;
+          break;
+        }
         const void* xs = a.src == ADST_BUF_NONE ? nullptr : buffer(a.src);
         if (c.shape.limit && !adjoint_applies_limit(c.shape, dparams != nullptr)) {
           // the branch each point took at step t (otherwise applied by the

@@ -131,6 +131,21 @@ inline bool make_grid(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int
   return *blocks > 0 && *blocks <= INT32_MAX;
 }
 
+// As make_grid, with the rows per chunk halved while the launch has fewer
+// workgroups (waves) than fill the chip: a launch of few waves takes the time
+// of one, the chunk's rows and those beyond its ends (1000 x 1000 f64 under the
+// limiter, T = 60: 1.92 -> 0.84 ms). Half and twice the count were within 4%
+// for the variable coefficients.
+constexpr int kFillWaves = 2048;
+inline bool make_grid_fit(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows = kRows) {
+  if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
+  while (rows > kEdgeRows && *blocks < kFillWaves) {
+    rows = rows / 2 < kEdgeRows ? kEdgeRows : rows / 2;
+    if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
+  }
+  return true;
+}
+
 // The V elements from column c0 (a multiple of V) of the row at src, by one
 // 16-byte load clamped into the row. VEC: nx is a multiple of V and rows
 // are 16-byte aligned, so a block is in the grid or outside it; else the load

@@ -62,8 +62,7 @@ hipError_t march_launch(const StepShape& s, const R* x, R* y, hipStream_t st) {
   if (ADJ && s.nx <= G::V) return hipErrorInvalidValue;  // a lane would hold both ring columns
   MarchGrid g;
   int64_t blocks;
-  if (!make_grid(s.nx, s.ny, G::OW, &g, &blocks))
-    return hipErrorInvalidValue;
+  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks)) return hipErrorInvalidValue;
   if (rows_aligned<R>(s.nx, x, y))
     jacobi_march<R, K, ADJ, true><<<dim3((unsigned)blocks), dim3(kLanes), 0, st>>>(
         x, y, s.nx, s.ny, g, R(s.p0), {});
@@ -263,7 +262,10 @@ hipError_t lim_adjoint_launch(const StepShape& s, const R* x, const R* g, R* gp,
   constexpr int V = 16 / sizeof(R), OW = kLanes * V - 2 * V;
   MarchGrid grid;
   int64_t blocks;
-  if (!make_grid(s.nx, s.ny, OW, &grid, &blocks, kLimRows)) return hipErrorInvalidValue;
+  // the slots of dL/dw belong to chunks of kLimRows
+  if (!(dp_part ? make_grid(s.nx, s.ny, OW, &grid, &blocks, kLimRows)
+                : make_grid_fit(s.nx, s.ny, OW, &grid, &blocks, kLimRows)))
+    return hipErrorInvalidValue;
   const bool vec = rows_aligned<R>(s.nx, x, g) && rows_aligned<R>(s.nx, gp, nullptr);
   const dim3 gr((unsigned)blocks), bl(kLanes);
   const R w = R(s.p0), lo = R(s.lo), hi = R(s.hi);

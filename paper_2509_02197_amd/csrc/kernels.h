@@ -101,6 +101,15 @@ hipError_t launch_jacobi_dp_adjoint(const StepShape& s, const void* x, const voi
                                     hipStream_t stream);
 int64_t jacobi_x_adjoint_slots(const StepShape& s);
 
+// Jacobi, two of those steps (both under the limiter, or both with dL/dw's
+// shares) in one launch: g_prev = J_{t-1}^T (m_{t-1} * J_t^T (m_t * g_next)),
+// x1 = x_{t-1}, x2 = x_{t-2} (jacobi_pair.hip). jacobi_pairs_adjoint tells
+// whether the shape takes it.
+bool jacobi_pairs_adjoint(const StepShape& s, bool dparams);
+hipError_t launch_jacobi_pair_adjoint(const StepShape& s, const void* x1, const void* x2,
+                                      const void* g_next, void* g_prev, double* dp_part,
+                                      bool dp_first, hipStream_t stream);
+
 // g_prev = J_t^T g_next with x = x_{t-1} (may be null when the kind's adjoint
 // reads no state and neither dK nor the constants' gradients are asked for).
 // dK (nullable) is accumulated: dK = (dk_first ? 0 : dK) + contribution of

@@ -43,7 +43,7 @@ namespace {
 // us, storing both states 300 / 288 / 268), and grids that give a launch
 // fewer waves than the chip holds take shorter ones (1023 x 1537 f64: 42 us
 // with 96 rows, 21 with 24).
-constexpr int kVdRows = 96, kVdStoreRows = 128, kVdMinRows = 12, kVdWaves = 2048;
+constexpr int kVdRows = 96, kVdStoreRows = 128;
 constexpr int kVdAhead = 4; // rows requested ahead
 
 // Terms of the edges of one row: to the row after it (n, ne, nw) and along it
@@ -209,12 +209,8 @@ hipError_t vd_run(const StepShape& s, const R* x, const R* K, R* y, R* mid, hipS
   constexpr int V = 16 / (int)sizeof(R), OW = kLanes * V - 2 * V;
   MarchGrid g;
   int64_t blocks;
-  int rows = mid ? kVdStoreRows : kVdRows;
-  if (!make_grid(s.nx, s.ny, OW, &g, &blocks, rows)) return hipErrorInvalidValue;
-  while (rows > kVdMinRows && blocks < kVdWaves) {
-    rows /= 2;
-    if (!make_grid(s.nx, s.ny, OW, &g, &blocks, rows)) return hipErrorInvalidValue;
-  }
+  if (!make_grid_fit(s.nx, s.ny, OW, &g, &blocks, mid ? kVdStoreRows : kVdRows))
+    return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kLanes);
   const R dt = R(s.p0), ca = R(1) / R(3), cd = R(1) / R(12);
   const bool vec = rows_aligned<R>(s.nx, x, K) && rows_aligned<R>(s.nx, y, mid);

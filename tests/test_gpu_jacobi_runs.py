@@ -1,5 +1,5 @@
-"""Jacobi forward launches under the limiter and store-through runs: several
-steps per launch, bit-identical to one launch per step, x_T bit for bit and
+"""Jacobi forward launches under the limiter, store-through runs and pairs of
+adjoint steps that read state: several steps per launch, bit-identical to one launch per step, x_T bit for bit and
 gradients within 1e-12 (fp64) / 1e-5 (fp32) of the oracle. Step counts reach
 every depth (2 to 6 steps, runs of 2 to 4 kept states); shapes sit around a
 strip's columns (116 to 124, 240 to 248) and a chunk's rows (48, 12, 6).
@@ -62,6 +62,9 @@ def test_runs(dtype, shape, name, opt, T, slots, sched):
     assert a["info"]["fwd_kernels"] <= b["info"]["fwd_kernels"] == b["info"]["fwd_steps_total"]
     if inp["x0"].size >= 1024:
         assert a["info"]["fwd_kernels"] < b["info"]["fwd_kernels"]
+        # adjoint steps pair up, with dL/dw in single precision only
+        pairs = name == "lim" or dtype == F32
+        assert (a["info"]["adj_kernels"] < T) == pairs and b["info"]["adj_kernels"] == T
     for key in ("dx0", "xT", "dparams"):
         if a[key] is not None:
             assert np.array_equal(a[key], b[key]), key
