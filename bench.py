@@ -517,8 +517,9 @@ def rocprof_label(name):
     m = re.match(r"(\w+)<(.*)>$", n)
     base, targs = (m.group(1), [a.strip() for a in m.group(2).split(",")]) if m else (n, [])
     t = lambda i: targs[i] == "true"  # noqa: E731
-    if base == "fwd_allencahn3d7_n":   # <R, K, RPT, NZ, NT, ST>
-        return f"fwd_allencahn3d7_n<{targs[1]}" + (",store>" if t(5) else ">")
+    if base == "fwd_allencahn3d7_n":   # <R, K, RPT, (NZ,) NT, ST, ...>
+        nt_st = [a for a in targs if a in ("true", "false")]
+        return f"fwd_allencahn3d7_n<{targs[1]}" + (",store>" if nt_st[1] == "true" else ">")
     if base == "fwd_vardiff2d9_x2":    # <R, TR, NT, ST>
         return "fwd_vardiff2d9_x2" + ("<store>" if t(3) else "")
     if base == "jacobi_march":         # <R, K, ADJ, VEC, LIM, ST, ...>

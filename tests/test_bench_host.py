@@ -73,6 +73,17 @@ def test_rocprof_names_map_to_library_labels(name, label):
     assert bench.rocprof_label(name) == label
 
 
+@pytest.mark.parametrize("name,label", [
+    ("fwd_allencahn3d7_n<double, 2, 4, false, true, 8>(x)", "fwd_allencahn3d7_n<2,store>"),
+    ("fwd_allencahn3d7_n<double, 3, 4, true, false, 4>(x)", "fwd_allencahn3d7_n<3>"),
+    ("jacobi_pair_adjoint<float, false, true>(x)", "jacobi_pair_adjoint<dp>"),
+    ("vd_march<double, true, true, false>(x)", "vd_march<store>"),
+    ("gs_pipe<double, true, 8>(x)", "gs_pipe<adj>"),
+])
+def test_labels_of_kernels_with_run_time_chunks(name, label):
+    assert bench.rocprof_label("void adst::(anonymous namespace)::" + name) == label
+
+
 def test_kernel_rows_from_rocpd_database(tmp_path):
     # rocprofv3 writes SQLite when no CSV format is asked for: the summary
     # aggregates its kernel dispatches per name
