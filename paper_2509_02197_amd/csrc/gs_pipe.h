@@ -142,6 +142,12 @@ __global__ __launch_bounds__(kGpLanes * NW) void gs_pipe(GpArgs p, R w) {
   if (t >= p.ngroups * p.ncol) return;
   // the ticket's group and column: by their sum, the smaller group first
   int d = 0, G = 0;
+  const int ramp = p.ngroups * (p.ngroups - 1) / 2;
+  if (p.ncol > p.ngroups && t >= ramp) {  // sums of ngroups tickets each
+    const int k = min((t - ramp) / p.ngroups, p.ncol - p.ngroups);
+    d = p.ngroups - 1 + k;
+    t -= ramp + k * p.ngroups;
+  }
   for (;; ++d) {
     G = max(0, d - p.ncol + 1);
     const int n = min(d, p.ngroups - 1) - G + 1;
