@@ -23,7 +23,8 @@ constexpr int kLimRows = 128;  // rows per chunk of the limiter's one-step adjoi
                                // 82.3 / 81.5 / 86.5 / 83.4 / 97.2 / 115.0 us
                                // per launch at 4096^2 f64 (before the hint,
                                // 192 was best: 90.4 against 92.7 us at 128)
-constexpr int kEdgeRows = 12;  // rows per chunk of the first and last strip
+constexpr int kEdgeRows = 12;  // rows per chunk of the first and last strip (fewer on
+                               // small grids, see make_grid_fit)
 constexpr int kEndRows = 6;    // rows of a strip's first and last chunk, whose
                                // blocks near the grid's top and bottom edge
                                // take the slower general path
@@ -68,7 +69,8 @@ struct Geom {
 // chunks [x*pi, (x+1)*pi), edge chunks first.
 struct MarchGrid {
   int ns, nedge, ce, ci, pe, pi;
-  int rows;  // rows per chunk of an interior strip (at most kRows)
+  int rows;  // rows per chunk of an interior strip
+  int erows; // and of the first and last strip
 };
 
 // This workgroup's strip and chunk of rows [r0, r1); false when the
@@ -85,7 +87,7 @@ __device__ inline bool march_item(const MarchGrid& g, int ny, int* strip, int* c
     *strip = (t / g.ce == 0) ? 0 : g.ns - 1;
     *chunk = t % g.ce;
     nch = g.ce;
-    mid = kEdgeRows;
+    mid = g.erows;
     if (item) *item = t;
   } else {
     const int t = xcd * g.pi + (slot - g.pe);
@@ -115,14 +117,16 @@ __device__ inline bool march_item(const MarchGrid& g, int ny, int* strip, int* c
 }
 
 // The work list for strips of ow output columns; false if it is too long.
-inline bool make_grid(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows = kRows) {
+inline bool make_grid(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows = kRows,
+                      int erows = kEdgeRows) {
   g->rows = rows;
+  g->erows = erows;
   g->ns = (nx + ow - 1) / ow;
   g->nedge = g->ns >= 2 ? 2 : 1;
   auto chunks = [&](int mid) {
     return ny > 2 * kEndRows ? 2 + (ny - 2 * kEndRows + mid - 1) / mid : 1;
   };
-  g->ce = chunks(kEdgeRows);
+  g->ce = chunks(erows);
   g->ci = chunks(rows);
   const int64_t E = int64_t(g->nedge) * g->ce, I = int64_t(g->ns - g->nedge) * g->ci;
   g->pe = (int)((E + kXcds - 1) / kXcds);
@@ -137,12 +141,17 @@ inline bool make_grid(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int
 // limiter, T = 60: 1.92 -> 0.84 ms). Half and twice the count were within 4%
 // for the variable coefficients.
 constexpr int kFillWaves = 2048;
+// With at most half a wave a SIMD even at kEdgeRows rows, every chunk is as
+// short as the end ones: twice the waves still have a SIMD each.
+constexpr int kFewWaves = 512;
 inline bool make_grid_fit(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows = kRows) {
   if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
   while (rows > kEdgeRows && *blocks < kFillWaves) {
     rows = rows / 2 < kEdgeRows ? kEdgeRows : rows / 2;
     if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
   }
+  if (rows <= kEdgeRows && *blocks < kFewWaves)
+    return make_grid(nx, ny, ow, g, blocks, kEndRows, kEndRows);
   return true;
 }
 
