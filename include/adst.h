@@ -280,7 +280,9 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
  * beyond workspace_bytes overlaps one of its arrays, runs the level launches;
  * the results are the same bit for bit. About half a state of 8-byte values
  * (a whole one of 4-byte values) plus a few percent. 0 for the other kinds, for
- * steps <= 0 and for an invalid problem (no error is recorded). Host only. */
+ * grids whose persistent launch would exceed the 32-bit dispatch grid or the
+ * kernel's 32-bit indices, for steps <= 0 and for an invalid problem (no error is
+ * recorded). Host only. */
 uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps);
 
 /* x_T after `steps` forward steps: the unmodified program whose gradient

@@ -887,7 +887,8 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
 uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps) {
   Checked c;
   if (check_problem(prob, 0, &c) != ADST_OK || !c.in_place || steps <= 0) return 0;
-  return gs_pipe_bytes(c.shape, steps) + 128;  // and its alignment
+  const uint64_t bytes = gs_pipe_bytes(c.shape, steps);
+  return bytes ? bytes + 128 : 0;  // and its alignment
 }
 
 adst_status adst_forward(const adst_problem* prob, const void* x0, const void* coeff,

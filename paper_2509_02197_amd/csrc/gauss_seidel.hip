@@ -329,8 +329,8 @@ struct GsGeom {
 GsGeom gs_geom(const StepShape& s) {
   GsGeom g;
   g.V = s.dtype == ADST_F64 ? 2 : 4;
-  g.nb = (s.nx + g.V - 1) / g.V;
-  g.nti = (s.ny + kGsLanes - 1 + kGsRows - 1) / kGsRows;
+  g.nb = (int)((int64_t(s.nx) + g.V - 1) / g.V);  // extents go up to INT32_MAX
+  g.nti = (int)((int64_t(s.ny) + kGsLanes - 1 + kGsRows - 1) / kGsRows);
   g.ntj = (g.nb + kGsLanes - 1) / kGsLanes;
   return g;
 }

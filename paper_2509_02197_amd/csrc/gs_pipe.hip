@@ -85,29 +85,43 @@ constexpr int kGpMaxPhases = 256;
 constexpr int kGpWide = 8, kGpNarrow = 4, kGpCus = 256;
 
 struct GpGeom {
-  int ngroups, ncol, nj;
+  int64_t ngroups, ncol, nj;
   uint64_t flag_bytes, bytes;  // flags; flags and halo
 };
 
 GpGeom gp_geom(const StepShape& s, int nph, int nwaves) {
-  GpGeom g;
-  const int isz = s.dtype == ADST_F64 ? 8 : 4, nc = kGpLanes * 16 / isz, S = kGpQ * nwaves;
+  GpGeom g{};
+  const int64_t isz = s.dtype == ADST_F64 ? 8 : 4, nc = kGpLanes * 16 / isz, S = kGpQ * nwaves;
   g.ngroups = (nph + S - 1) / S;
-  g.ncol = 0;
-  for (int k = 0; k < g.ngroups; ++k) {  // as j_lo and j_hi of the kernel
-    const int nw = (std::min(S, nph - k * S) + kGpQ - 1) / kGpQ;
-    const int lo = k * S / nc, hi = (s.nx - 1 + k * S + nw * kGpQ - 1) / nc;
+  for (int64_t k = 0; k < g.ngroups; ++k) {  // as j_lo and j_hi of the kernel
+    const int64_t nw = (std::min(S, nph - k * S) + kGpQ - 1) / kGpQ;
+    const int64_t lo = k * S / nc, hi = (s.nx - 1 + k * S + nw * kGpQ - 1) / nc;
     g.ncol = std::max(g.ncol, hi - lo + 1);
     g.nj = hi + 1;
   }
   g.flag_bytes = (uint64_t(g.ngroups) * g.ncol + 1) * kGpFlagInts * sizeof(int);
-  g.bytes = g.flag_bytes + uint64_t(std::min(2, g.ngroups)) * g.nj * S * uint64_t(s.ny) * isz;
+  g.bytes = g.flag_bytes + uint64_t(std::min<int64_t>(2, g.ngroups)) * g.nj * S * uint64_t(s.ny) * isz;
   return g;
 }
 
 int gp_waves(const StepShape& s, int nph) {
   const GpGeom g = gp_geom(s, nph, kGpNarrow);
   return g.ngroups * g.ncol <= kGpCus ? kGpNarrow : kGpWide;
+}
+
+// Whether launches of up to kGpMaxPhases phases can run the shape; where not,
+// the level launches do. The kernel's rows, columns and macro times are
+// 32-bit: they reach a few hundred beyond the grid's extent. A launch has
+// fewer than 2^32 work-items (HIP refuses more: 3 x 160,000,000 f64 with 100
+// phases would have 1.04 of that many).
+constexpr int32_t kGpMaxExtent = INT32_MAX - 4 * kGpMaxPhases;
+bool gp_fits(const StepShape& s, int nph) {
+  if (s.nx > kGpMaxExtent || s.ny > kGpMaxExtent) return false;
+  for (const int nw : {kGpNarrow, kGpWide}) {
+    const GpGeom g = gp_geom(s, nph, nw);
+    if (uint64_t(g.ngroups) * g.ncol * kGpLanes * nw >= (uint64_t(1) << 32)) return false;
+  }
+  return true;
 }
 
 template <class R, bool ADJ>
@@ -120,7 +134,7 @@ hipError_t gp_run(const StepShape& s, R* buf, const R* src, int phases, void* sc
     if (z != hipSuccess) return z;
     const GpArgs a{buf, ph == 0 ? src : buf, static_cast<int*>(scratch),
                    static_cast<char*>(scratch) + g.flag_bytes, s.nx, s.ny, n, ph, phases,
-                   g.ngroups, g.ncol, g.nj};
+                   (int)g.ngroups, (int)g.ncol, (int)g.nj};
     const dim3 grid((unsigned)(g.ngroups * g.ncol)), block(kGpLanes * nw);
     if (nw == kGpNarrow)
       gs_pipe<R, ADJ, kGpNarrow><<<grid, block, 0, st>>>(a, R(s.p0));
@@ -137,6 +151,7 @@ hipError_t gp_run(const StepShape& s, R* buf, const R* src, int phases, void* sc
 uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps) {
   if (sweeps <= 0) return 0;
   const int phases = (int)std::min<int64_t>(int64_t(sweeps) + 1, kGpMaxPhases);
+  if (!gp_fits(s, phases)) return 0;
   // of a run of at most that many phases, with either workgroup
   return std::max(gp_geom(s, phases, kGpNarrow).bytes, gp_geom(s, phases, kGpWide).bytes);
 }

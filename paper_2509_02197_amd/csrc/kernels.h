@@ -144,7 +144,8 @@ hipError_t launch_finalize(const double* partials, int32_t nparts, double* loss,
 // With scratch (gs_pipe_bytes(s, n) bytes for some n >= sweeps, 128-byte
 // aligned) each runs as one persistent launch per 256 phases (gs_pipe.hip);
 // without (null), as a sequence of wavefront launches, one per level, that
-// pipelines the sweeps. gs_kernel_launches counts the levels.
+// pipelines the sweeps. gs_kernel_launches counts the levels. gs_pipe_bytes is
+// 0 where the persistent launch cannot run the shape.
 hipError_t launch_gs_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
                              void* scratch, hipStream_t stream);
 hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, void* scratch,

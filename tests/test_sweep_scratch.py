@@ -1,0 +1,28 @@
+"""adst_sweep_workspace_bytes on the host: the scratch with which the in-place
+kind's sweeps run as one persistent launch, 0 where that launch cannot run."""
+import pytest
+
+import paper_2509_02197_amd as adst
+
+GS = adst.ADST_GAUSSSEIDEL2D5
+F64, F32 = adst.ADST_F64, adst.ADST_F32
+
+
+def scratch(dtype, nx, ny, T):
+    return adst.adst_sweep_workspace_bytes(adst.make_problem(GS, dtype, (nx, ny, 1)), T)
+
+
+@pytest.mark.parametrize("dtype", [F64, F32])
+def test_extents_near_the_32_bit_limit_have_no_persistent_launch(dtype):
+    for nx, ny in [(2**31 - 1, 1), (2**31 - 200, 1), (1, 2**31 - 1), (1, 2**31 - 200)]:
+        for T in (1, 100, 1000):
+            assert scratch(dtype, nx, ny, T) == 0, (nx, ny, T)
+
+
+def test_launches_beyond_the_dispatch_grid_have_no_persistent_launch():
+    """Strips of 128 (f64) or 256 (f32) columns, groups of 16 phases of 512
+    work-items each: these would have 2^32 work-items or more."""
+    for dtype, nx, ny, T in [(F64, 160_000_000, 3, 100), (F64, 80_000_000, 20, 255),
+                             (F64, 700_000_000, 3, 100), (F32, 320_000_000, 3, 100),
+                             (F32, 160_000_000, 10, 1000)]:
+        assert scratch(dtype, nx, ny, T) == 0, (dtype, nx, ny, T)
