@@ -886,7 +886,10 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
 
 uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps) {
   Checked c;
-  if (check_problem(prob, 0, &c) != ADST_OK || !c.in_place || steps <= 0) return 0;
+  const std::string error = g_last_error;  // a size query leaves it as it was
+  const adst_status st = check_problem(prob, 0, &c);
+  g_last_error = error;
+  if (st != ADST_OK || !c.in_place || steps <= 0) return 0;
   const uint64_t bytes = gs_pipe_bytes(c.shape, steps);
   return bytes ? bytes + 128 : 0;  // and its alignment
 }

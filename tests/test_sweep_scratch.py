@@ -26,3 +26,19 @@ def test_launches_beyond_the_dispatch_grid_have_no_persistent_launch():
                              (F64, 700_000_000, 3, 100), (F32, 320_000_000, 3, 100),
                              (F32, 160_000_000, 10, 1000)]:
         assert scratch(dtype, nx, ny, T) == 0, (dtype, nx, ny, T)
+
+
+def test_an_invalid_problem_gets_0_and_leaves_the_last_error():
+    """Both after a call that failed and after one that succeeded."""
+    good = adst.make_problem(GS, F64, (40, 30, 1))
+    for steps, bad in [(5, (0, 30, 1)), (5, (40, 30, 2))]:
+        adst.adst_plan(good, 5, 0, 0)
+        assert adst.adst_sweep_workspace_bytes(adst.make_problem(GS, F64, bad), steps) == 0
+        assert adst.adst_last_error() == ""
+        with pytest.raises(adst.AdstError):
+            adst.adst_plan(good, -1, 0, 0)
+        error = adst.adst_last_error()
+        assert "steps" in error
+        assert adst.adst_sweep_workspace_bytes(adst.make_problem(GS, F64, bad), steps) == 0
+        assert adst.adst_last_error() == error
+    assert scratch(F64, 40, 30, 0) == 0 and scratch(F64, 40, 30, -1) == 0
