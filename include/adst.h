@@ -278,11 +278,13 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
  * wavefront level (400 x 400 f64, 100 sweeps and their reverse: 7.4 ms with
  * level launches). Optional: a call given less, or given a ws whose part
  * beyond workspace_bytes overlaps one of its arrays, runs the level launches;
- * the results are the same bit for bit. About half a state of 8-byte values
- * (a whole one of 4-byte values) plus a few percent. 0 for the other kinds, for
- * grids whose persistent launch would exceed the 32-bit dispatch grid or the
- * kernel's 32-bit indices, for steps <= 0 and for an invalid problem (no error is
- * recorded). Host only. */
+ * the results are the same bit for bit. Up to about a quarter of a state of
+ * 8-byte values and an eighth of one of 4-byte values on wide grids, up to a
+ * whole state below a hundred columns. At most two states and 64 KiB, or 1 MiB where
+ * that is more: 0 for a grid of a few columns that would need more, for one
+ * whose persistent launch would exceed the 32-bit dispatch grid or the
+ * kernel's 32-bit indices, for the other kinds, for steps <= 0 and for an
+ * invalid problem (no error is recorded). Host only. */
 uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps);
 
 /* x_T after `steps` forward steps: the unmodified program whose gradient

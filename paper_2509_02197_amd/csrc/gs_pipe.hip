@@ -148,12 +148,28 @@ hipError_t gp_run(const StepShape& s, R* buf, const R* src, int phases, void* sc
 
 }  // namespace
 
+// The halo is two groups' phases by rows for every strip: on wide grids a
+// quarter of an f64 state and an eighth of an f32 one with eight waves, half
+// that with four (4096 x 4096, T = 100: 34.6 of 134 MB, 4.5 of 67), but a
+// strip however narrow the grid is and one more per 128 or 256 phases it has
+// moved left by. Grids of fewer than 16 columns would need several states (3
+// columns f64, T = 200: 10), and run the level launches beyond this bound
+// (1,000,000 rows of 4 f64, T = 20: 210 ms forward as one launch, 258 as
+// levels).
+uint64_t gp_most_bytes(const StepShape& s) {
+  const uint64_t state = uint64_t(s.nx) * s.ny * (s.dtype == ADST_F64 ? 8 : 4);
+  return std::max<uint64_t>(2 * state + (64 << 10), 1 << 20);
+}
+
+// gp_waves picks eight waves only above some number of phases: a run of
+// fewer phases never needs more than this.
 uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps) {
   if (sweeps <= 0) return 0;
   const int phases = (int)std::min<int64_t>(int64_t(sweeps) + 1, kGpMaxPhases);
   if (!gp_fits(s, phases)) return 0;
-  // of a run of at most that many phases, with either workgroup
-  return std::max(gp_geom(s, phases, kGpNarrow).bytes, gp_geom(s, phases, kGpWide).bytes);
+  uint64_t bytes = gp_geom(s, phases, kGpNarrow).bytes;
+  if (gp_waves(s, phases) == kGpWide) bytes = std::max(bytes, gp_geom(s, phases, kGpWide).bytes);
+  return bytes <= gp_most_bytes(s) ? bytes : 0;
 }
 
 hipError_t gs_pipe_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,

@@ -42,3 +42,24 @@ def test_an_invalid_problem_gets_0_and_leaves_the_last_error():
         assert adst.adst_sweep_workspace_bytes(adst.make_problem(GS, F64, bad), steps) == 0
         assert adst.adst_last_error() == error
     assert scratch(F64, 40, 30, 0) == 0 and scratch(F64, 40, 30, -1) == 0
+
+
+def test_scratch_is_bounded_and_of_the_documented_size():
+    """Never more than two states and 64 KiB (or 1 MiB); at most about a
+    quarter of an f64 state and an eighth of an f32 one on wide grids, a state or less from 48
+    columns on at 200 sweeps."""
+    for dtype, isz in ((F64, 8), (F32, 4)):
+        for nx in (1, 3, 4, 7, 8, 15, 16, 24, 48, 127, 129, 400, 5000, 100_000):
+            for ny in (1, 3, 50, 5000, 20_000, 300_000):
+                if nx * ny > 2**30:
+                    continue
+                state = nx * ny * isz
+                for T in (1, 9, 100, 200, 255, 1000):
+                    b = scratch(dtype, nx, ny, T)
+                    assert b <= max(2 * state + (64 << 10), 1 << 20) + 128, (nx, ny, T)
+                    if 48 <= nx <= 5000 and 48 <= ny <= 5000 and T <= 200:
+                        assert 0 < b <= state + 4096, (nx, ny, T)
+        assert scratch(dtype, 3, 1_000_000, 255) == 0
+        for n in (4096, 20_000):
+            share = scratch(dtype, n, n, 100) / (n * n * isz)
+            assert 0 < share <= (0.28 if dtype == F64 else 0.14)
