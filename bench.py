@@ -234,8 +234,9 @@ def run_workload(adst, torch, w, opts, steps, warmup, traced_calls, say, inp=Non
     prob = adst.make_problem(w.kind, w.dtype, dims_of(w.shape), w.params, flags, lim)
     grads = (adst.ADST_GRAD_COEFF if w.want_dK else 0) | (adst.ADST_GRAD_PARAMS if want_dp else 0)
     info = adst.adst_plan(prob, w.steps, budget, sched, grads)
-    ws = torch.empty(info.workspace_bytes + adst.adst_sweep_workspace_bytes(prob, w.steps),
-                     dtype=torch.uint8, device=dev)
+    ws = torch.empty(info.workspace_bytes, dtype=torch.uint8, device=dev)
+    extra = adst.adst_sweep_workspace_bytes(prob, w.steps)  # the in-place kind's
+    scratch = torch.empty(extra, dtype=torch.uint8, device=dev) if extra else None
     dx0 = torch.empty_like(x0)
     dK = torch.empty_like(x0) if w.want_dK else None
     L = torch.empty((), dtype=torch.float64, device=dev)
@@ -244,7 +245,7 @@ def run_workload(adst, torch, w, opts, steps, warmup, traced_calls, say, inp=Non
 
     def call(p):
         return adst.adst_vjp(p, x0, K, w.steps, w.loss, aux, budget, sched, dx0, dK, None, L, dP,
-                             ws, ws.numel(), stream)
+                             ws, ws.numel(), stream, scratch=scratch, scratch_bytes=extra)
 
     for _ in range(warmup):
         call(prob)
@@ -324,7 +325,7 @@ def run_workload(adst, torch, w, opts, steps, warmup, traced_calls, say, inp=Non
                      "share": round(k["ms_sum"] / max(sum(q["ms_sum"] for q in kl), 1e-9), 4)}
                     for k in kl],
     }
-    del x0, K, aux, ws, dx0, dK, L, dP
+    del x0, K, aux, ws, scratch, dx0, dK, L, dP
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     return res, inp

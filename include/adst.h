@@ -272,19 +272,17 @@ adst_status adst_plan_actions(const adst_problem* prob, int32_t steps, uint64_t 
                               int32_t sched, int32_t grads, adst_action* out, int64_t cap,
                               int64_t* n_out);
 
-/* Bytes of workspace, beyond workspace_bytes (adst_vjp) or
- * fwd_workspace_bytes (adst_forward), with which the in-place kind's sweeps
- * run as one persistent launch per 256 sweeps instead of one launch per
- * wavefront level (400 x 400 f64, 100 sweeps and their reverse: 7.4 ms with
- * level launches). Optional: a call given less, or given a ws whose part
- * beyond workspace_bytes overlaps one of its arrays, runs the level launches;
- * the results are the same bit for bit. Up to about a quarter of a state of
- * 8-byte values and an eighth of one of 4-byte values on wide grids, up to a
- * whole state below a hundred columns. At most two states and 64 KiB, or 1 MiB where
- * that is more: 0 for a grid of a few columns that would need more, for one
- * whose persistent launch would exceed the 32-bit dispatch grid or the
- * kernel's 32-bit indices, for the other kinds, for steps <= 0 and for an
- * invalid problem (no error is recorded). Host only. */
+/* Bytes of scratch (adst_forward_scratch, adst_vjp_scratch) with which the
+ * in-place kind's sweeps run as one persistent launch per 256 sweeps instead
+ * of one launch per wavefront level (400 x 400 f64, 100 sweeps and their
+ * reverse: 7.4 ms with level launches, 1.07 as one). The results are the same
+ * bit for bit. Up to about a quarter of a state of 8-byte values and an eighth
+ * of one of 4-byte values on wide grids, up to a whole state below a hundred
+ * columns. At most two states and 64 KiB, or 1 MiB where that is more: 0 for a
+ * grid of a few columns that would need more, for one whose persistent launch
+ * would exceed the 32-bit dispatch grid or the kernel's 32-bit indices, for
+ * the other kinds, for steps <= 0 and for an invalid problem (no error is
+ * recorded). Host only. */
 uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps);
 
 /* x_T after `steps` forward steps: the unmodified program whose gradient
@@ -293,12 +291,20 @@ uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps);
  * x0 and xT are [nz][ny][nx] arrays of the working precision; coeff is K for
  * VARDIFF2D9 and must be NULL-or-ignored otherwise. ws must hold
  * adst_plan_info.fwd_workspace_bytes (one state when steps >= 2, else 0;
- * always 0 for the in-place kind, which runs in xT and uses ws only as
- * adst_sweep_workspace_bytes says).
+ * always 0 for the in-place kind, which runs in xT); nothing beyond that
+ * many bytes of it is written, however large ws_bytes is.
  * Errors: as adst_plan, plus ADST_ERR_WORKSPACE and ADST_ERR_HIP. */
 adst_status adst_forward(const adst_problem* prob, const void* x0, const void* coeff,
                          int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
                          hipStream_t stream);
+
+/* adst_forward with scratch for the in-place kind's sweeps: device memory that
+ * is clobbered, apart from ws and from the call's arrays (ADST_ERR_ARG where it
+ * overlaps them). Given less than adst_sweep_workspace_bytes, or NULL, and for
+ * the other kinds, the call is adst_forward and touches none of it. */
+adst_status adst_forward_scratch(const adst_problem* prob, const void* x0, const void* coeff,
+                                 int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
+                                 void* scratch, uint64_t scratch_bytes, hipStream_t stream);
 
 /* Forward sweep, loss, and reverse sweep under the budget, enqueued on
  * `stream`: the vector-Jacobian product of one scalar output with respect to
@@ -314,7 +320,8 @@ adst_status adst_forward(const adst_problem* prob, const void* x0, const void* c
  * ADST_GRAD_PARAMS; NULL = not requested). The plan is the one adst_plan
  * gives for grads = (dcoeff ? ADST_GRAD_COEFF : 0) | (dparams ?
  * ADST_GRAD_PARAMS : 0). ws must hold
- * adst_plan_info.workspace_bytes and is clobbered. dx0 doubles as one of the
+ * adst_plan_info.workspace_bytes, which are clobbered; nothing beyond that many
+ * bytes of it is written, however large ws_bytes is. dx0 doubles as one of the
  * two adjoint buffers (for the in-place kind, the only one: the reverse
  * sweeps run in place in dx0). steps = 0 is valid: dx0 = seed, dK = 0.
  * info (optional, host) receives the plan; with ADST_TRACE it also receives
@@ -326,6 +333,15 @@ adst_status adst_vjp(const adst_problem* prob, const void* x0, const void* coeff
                      void* dx0, void* dcoeff, void* xT, double* loss_dev, double* dparams,
                      void* ws, uint64_t ws_bytes, hipStream_t stream, adst_plan_info* info);
 
+/* adst_vjp with scratch for the in-place kind's sweeps, as
+ * adst_forward_scratch. */
+adst_status adst_vjp_scratch(const adst_problem* prob, const void* x0, const void* coeff,
+                             int32_t steps, int32_t loss, const void* loss_aux,
+                             uint64_t mem_budget_bytes, int32_t sched, void* dx0, void* dcoeff,
+                             void* xT, double* loss_dev, double* dparams, void* ws,
+                             uint64_t ws_bytes, void* scratch, uint64_t scratch_bytes,
+                             hipStream_t stream, adst_plan_info* info);
+
 /* ---- Without allocation -------------------------------------------------
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): adst_vjp
@@ -334,8 +350,8 @@ adst_status adst_vjp(const adst_problem* prob, const void* x0, const void* coeff
  * library's code object: each GPU the library runs on holds its own copy
  * until the process ends; its address is looked up on the call's first use
  * of a device, with no allocation. Arguments, outputs, plan and results are
- * those of adst_vjp with the same arguments (bit for bit: the same kernels
- * run). No part of the workspace needs to start at zero: every value the
+ * those of adst_vjp with the same arguments (bit for bit; the array's part
+ * beyond the plan's workspace serves as adst_vjp_scratch's scratch). No part of the workspace needs to start at zero: every value the
  * call reads from it was written earlier in the same call. Every call on a
  * GPU shares that GPU's array, so calls that overlap on one GPU (on
  * different streams, or from several host threads) race and must be

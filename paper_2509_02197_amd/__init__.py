@@ -28,7 +28,8 @@ ADST_BUF_NONE, ADST_BUF_X0, ADST_BUF_W0, ADST_BUF_W1, ADST_BUF_XT, ADST_BUF_SLOT
 
 EXPORTED = ("adst_plan", "adst_plan_actions", "adst_forward", "adst_vjp", "adst_ilp_solve",
             "adst_trace_kernels", "adst_copy", "adst_vjp_static_ws", "adst_status_str",
-            "adst_last_error", "adst_sweep_workspace_bytes")
+            "adst_last_error", "adst_sweep_workspace_bytes", "adst_forward_scratch",
+            "adst_vjp_scratch")
 ADST_STATIC_WS_BYTES = 64 << 20
 PHASE_NAMES = ("forward sweep", "recomputation", "adjoint", "loss and seed", "constants")
 ILP_EVENTS = {"alloc": 0, "free": 1, "produce": 2, "drop": 3, "recompute": 4,
@@ -112,6 +113,9 @@ def lib():
     L.adst_forward.argtypes = [P(adst_problem), vp, vp, i32, vp, vp, u64, vp]
     L.adst_vjp.argtypes = [P(adst_problem), vp, vp, i32, i32, vp, u64, i32, vp, vp, vp, vp, vp, vp,
                            u64, vp, P(adst_plan_info)]
+    L.adst_forward_scratch.argtypes = [P(adst_problem), vp, vp, i32, vp, vp, u64, vp, u64, vp]
+    L.adst_vjp_scratch.argtypes = [P(adst_problem), vp, vp, i32, i32, vp, u64, i32, vp, vp, vp, vp,
+                                   vp, vp, u64, vp, u64, vp, P(adst_plan_info)]
     L.adst_ilp_solve.argtypes = [P(adst_ilp_array), i32, P(adst_ilp_event), i64, ctypes.c_double,
                                  P(i32), P(adst_ilp_info)]
     L.adst_vjp_static_ws.argtypes = [P(adst_problem), vp, vp, i32, i32, vp, u64, i32, vp, vp, vp,
@@ -119,7 +123,8 @@ def lib():
     L.adst_trace_kernels.argtypes = [P(adst_kernel_stat), i32, P(i32)]
     L.adst_copy.argtypes = [vp, vp, u64, vp]
     for f in ("adst_plan", "adst_plan_actions", "adst_forward", "adst_vjp", "adst_ilp_solve",
-              "adst_trace_kernels", "adst_copy", "adst_vjp_static_ws"):
+              "adst_trace_kernels", "adst_copy", "adst_vjp_static_ws", "adst_forward_scratch",
+              "adst_vjp_scratch"):
         getattr(L, f).restype = ctypes.c_int
     L.adst_sweep_workspace_bytes.argtypes = [P(adst_problem), i32]
     L.adst_sweep_workspace_bytes.restype = u64
@@ -198,23 +203,34 @@ def adst_plan_actions(prob, steps, mem_budget_bytes, sched, grads=0):
 
 
 def adst_sweep_workspace_bytes(prob, steps):
-    """Workspace beyond the plan's with which the in-place kind's sweeps run
-    as one launch (0 for the other kinds)."""
+    """Scratch with which the in-place kind's sweeps run as one launch (0 for
+    the other kinds, and where that launch cannot run)."""
     return int(lib().adst_sweep_workspace_bytes(ctypes.byref(prob), steps))
 
 
-def adst_forward(prob, x0, coeff, steps, xT, ws, ws_bytes, stream=None):
-    _check(lib().adst_forward(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, _ptr(xT),
-                              _ptr(ws), ws_bytes, _stream(stream)))
+def adst_forward(prob, x0, coeff, steps, xT, ws, ws_bytes, stream=None, scratch=None,
+                 scratch_bytes=0):
+    """adst_forward, or with scratch adst_forward_scratch."""
+    args = [ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, _ptr(xT), _ptr(ws), ws_bytes]
+    if scratch is None:
+        _check(lib().adst_forward(*args, _stream(stream)))
+    else:
+        _check(lib().adst_forward_scratch(*args, _ptr(scratch), scratch_bytes, _stream(stream)))
 
 
 def adst_vjp(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx0, dcoeff, xT,
-             loss_dev, dparams, ws, ws_bytes, stream=None, want_info=True):
+             loss_dev, dparams, ws, ws_bytes, stream=None, want_info=True, scratch=None,
+             scratch_bytes=0):
+    """adst_vjp, or with scratch adst_vjp_scratch."""
     info = adst_plan_info() if want_info else None
-    _check(lib().adst_vjp(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, loss, _ptr(loss_aux),
-                          mem_budget_bytes, sched, _ptr(dx0), _ptr(dcoeff), _ptr(xT),
-                          _ptr(loss_dev), _ptr(dparams), _ptr(ws), ws_bytes, _stream(stream),
-                          ctypes.byref(info) if info is not None else None))
+    args = [ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, loss, _ptr(loss_aux),
+            mem_budget_bytes, sched, _ptr(dx0), _ptr(dcoeff), _ptr(xT), _ptr(loss_dev),
+            _ptr(dparams), _ptr(ws), ws_bytes]
+    last = [_stream(stream), ctypes.byref(info) if info is not None else None]
+    if scratch is None:
+        _check(lib().adst_vjp(*args, *last))
+    else:
+        _check(lib().adst_vjp_scratch(*args, _ptr(scratch), scratch_bytes, *last))
     return info
 
 
@@ -315,54 +331,68 @@ def _check_tensors(x0, **others):
         raise ValueError(f"x0 must be on a GPU, not {x0.device}")
 
 
-def _workspace(ws, need, prob, steps, device, stream):
-    """(the workspace a call runs in, the one it hands back): ws where it
-    holds `need` bytes, else a new one. The in-place kind's calls run in one
-    with adst_sweep_workspace_bytes more, taken from torch's allocator where
-    ws is smaller and that much is free."""
+def _device_bytes(n, device, stream):
+    """n bytes for one call: given back to torch's allocator, they are reused
+    only when the stream they were used on is done."""
     import torch
-    extra = adst_sweep_workspace_bytes(prob, steps) if prob.kind == ADST_GAUSSSEIDEL2D5 else 0
-    given = ws is not None and ws.numel() >= need
-    if given and ws.numel() >= need + extra:
-        return ws, ws
-    roomy = None
-    if extra:
-        try:
-            roomy = torch.empty(need + extra, dtype=torch.uint8, device=device)
-        except torch.cuda.OutOfMemoryError:
-            pass
-    if roomy is not None and stream is not None:
-        # released to the allocator only when the stream it is used on is done
+    t = torch.empty(n, dtype=torch.uint8, device=device)
+    if stream is not None:
         handle = _stream(stream)
-        roomy.record_stream(torch.cuda.ExternalStream(handle, device=device) if handle
-                            else torch.cuda.default_stream(device))
-    if not given:
-        ws = roomy if roomy is not None else torch.empty(max(need, 1), dtype=torch.uint8,
-                                                         device=device)
-    return (roomy if roomy is not None else ws), ws
+        t.record_stream(torch.cuda.ExternalStream(handle, device=device) if handle
+                        else torch.cuda.default_stream(device))
+    return t
 
 
-def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, flags=0):
-    """x_T on the device of x0 (torch tensors, row-major)."""
+def _sweep_scratch(scratch, prob, steps, device, stream):
+    """The tensor the in-place kind's sweeps use beside the workspace, or None:
+    the caller's, or one taken from torch's allocator where that much is free
+    (none for scratch=False)."""
+    import torch
+    if prob.kind != ADST_GAUSSSEIDEL2D5 or scratch is False:
+        return None
+    if scratch is not None:
+        if not torch.is_tensor(scratch) or scratch.device != device or \
+                not scratch.is_contiguous():
+            raise ValueError(f"scratch must be a contiguous tensor on {device}")
+        return scratch
+    n = adst_sweep_workspace_bytes(prob, steps)
+    if n == 0:
+        return None
+    try:
+        return _device_bytes(n, device, stream)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
+def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, flags=0,
+            scratch=None):
+    """x_T on the device of x0 (torch tensors, row-major). scratch: as in vjp."""
     import torch
     _check_tensors(x0, coeff=coeff)
     prob = make_problem(kind, _dtype_code(x0), _dims(x0.shape), params, flags, lim)
     xT = torch.empty_like(x0)
     info = adst_plan(prob, steps, 1 << 62, ADST_SCHED_STORE_ALL)
-    ws, _ = _workspace(None, info.fwd_workspace_bytes, prob, steps, x0.device, stream)
-    adst_forward(prob, x0, coeff, steps, xT, ws, ws.numel(), stream)
+    ws = _device_bytes(max(info.fwd_workspace_bytes, 1), x0.device, stream)
+    scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
+    adst_forward(prob, x0, coeff, steps, xT, ws, info.fwd_workspace_bytes, stream, scratch,
+                 0 if scratch is None else scratch.nbytes)
     return xT
 
 
 def vjp(kind, x0, coeff=None, steps=1, loss=ADST_LOSS_HALF_SQ, aux=None, budget_bytes=None,
         sched=ADST_SCHED_AUTO, want_dcoeff=False, params=None, flags=0, stream=None, ws=None,
-        want_xT=True, want_dparams=False, lim=None):
+        want_xT=True, want_dparams=False, lim=None, scratch=None):
     """Allocate outputs and workspace with torch and run adst_vjp.
 
     budget_bytes=None means unlimited (store-all). Returns a dict with dx0,
     dK (or None), xT (None unless want_xT), loss (0-d device tensor),
-    dparams (device double[2], or None unless want_dparams), info and the
-    workspace."""
+    dparams (device double[2], or None unless want_dparams), info, the
+    workspace and scratch_bytes, what the call had beside the workspace. ws: a
+    uint8 tensor to run in, used where it holds the plan's workspace_bytes.
+    scratch: for the in-place kind, a uint8 tensor of
+    adst_sweep_workspace_bytes with which its sweeps run as one launch; None
+    takes that much from torch's allocator, False runs them as level launches,
+    without it."""
     import torch
     _check_tensors(x0, coeff=coeff, aux=aux)
     prob = make_problem(kind, _dtype_code(x0), _dims(x0.shape), params, flags, lim)
@@ -370,12 +400,16 @@ def vjp(kind, x0, coeff=None, steps=1, loss=ADST_LOSS_HALF_SQ, aux=None, budget_
         budget_bytes = (1 << 63)
     grads = (ADST_GRAD_COEFF if want_dcoeff else 0) | (ADST_GRAD_PARAMS if want_dparams else 0)
     info = adst_plan(prob, steps, budget_bytes, sched, grads)
-    run_ws, ws = _workspace(ws, info.workspace_bytes, prob, steps, x0.device, stream)
+    if ws is None or ws.numel() < info.workspace_bytes:
+        ws = _device_bytes(info.workspace_bytes, x0.device, stream)
+    scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
     dx0 = torch.empty_like(x0)
     dK = torch.empty_like(x0) if want_dcoeff else None
     xT = torch.empty_like(x0) if want_xT else None
     L = torch.empty((), dtype=torch.float64, device=x0.device)
     dp = torch.empty(2, dtype=torch.float64, device=x0.device) if want_dparams else None
     info = adst_vjp(prob, x0, coeff, steps, loss, aux, budget_bytes, sched, dx0, dK, xT, L, dp,
-                    run_ws, run_ws.numel(), stream)
-    return {"dx0": dx0, "dK": dK, "xT": xT, "loss": L, "dparams": dp, "info": info, "ws": ws}
+                    ws, ws.numel(), stream, scratch=scratch,
+                    scratch_bytes=0 if scratch is None else scratch.nbytes)
+    return {"dx0": dx0, "dK": dK, "xT": xT, "loss": L, "dparams": dp, "info": info, "ws": ws,
+            "scratch_bytes": 0 if scratch is None else scratch.nbytes}

@@ -450,22 +450,20 @@ Range range_of(const char* name, const void* p, uint64_t bytes) {
   return {name, lo, p ? lo + bytes : lo};
 }
 
-// The scratch with which the in-place kind's sweeps run as one launch: the
-// part of ws beyond the first `used` bytes, where it is large enough and
-// touches none of the call's arrays (a caller may pass a larger ws_bytes
-// whose tail it uses otherwise); null elsewhere, and the sweeps then run as
-// level launches.
-void* sweep_scratch(const Checked& c, int32_t steps, void* ws, uint64_t used, uint64_t ws_bytes,
-                    const std::vector<Range>& arrays) {
-  if (!c.in_place || !ws || ws_bytes < used) return nullptr;
+// The part of a caller's scratch with which the in-place kind's sweeps run as
+// one launch, aligned for it; null where there is none or too little (the
+// sweeps then run as level launches) and for the other kinds. bytes: how much
+// of it the sweeps may write.
+void* sweep_scratch(const Checked& c, int32_t steps, void* scratch, uint64_t scratch_bytes,
+                    uint64_t* bytes) {
+  *bytes = 0;
+  if (!c.in_place || !scratch) return nullptr;
   const uint64_t need = gs_pipe_bytes(c.shape, steps);
-  const uintptr_t lo = reinterpret_cast<uintptr_t>(ws) + used, end = lo + (ws_bytes - used);
-  const uintptr_t at = (lo + 127) / 128 * 128;
-  if (need == 0 || at > end || end - at < need) return nullptr;
-  const Range r = {"scratch", at, at + need};
-  for (const Range& a : arrays)
-    if (overlaps(r, a)) return nullptr;
-  return reinterpret_cast<void*>(at);
+  const uintptr_t p = reinterpret_cast<uintptr_t>(scratch);
+  const uint64_t skip = (128 - p % 128) % 128;
+  if (need == 0 || scratch_bytes < skip || scratch_bytes - skip < need) return nullptr;
+  *bytes = need;
+  return reinterpret_cast<void*>(p + skip);
 }
 
 // Every output range must be disjoint from every other output and from the
@@ -607,13 +605,14 @@ adst_status hip_fail(hipError_t e, const char* what) {
 namespace adst {
 namespace {
 
-// adst_vjp, with the workspace either the caller's (ws, ws_bytes) or, with
-// static_ws, this device's static workspace.
+// adst_vjp and adst_vjp_scratch, with the workspace either the caller's (ws,
+// ws_bytes) or, with static_ws, this device's static workspace, whose part
+// beyond the plan's bytes is the scratch.
 adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff, int32_t steps,
                      int32_t loss, const void* loss_aux, uint64_t mem_budget_bytes, int32_t sched,
                      void* dx0, void* dcoeff, void* xT, double* loss_dev, double* dparams,
-                     void* ws, uint64_t ws_bytes, bool static_ws, hipStream_t stream,
-                     adst_plan_info* info) {
+                     void* ws, uint64_t ws_bytes, void* scratch_in, uint64_t scratch_bytes,
+                     bool static_ws, hipStream_t stream, adst_plan_info* info) {
   const int32_t grads = (dcoeff ? ADST_GRAD_COEFF : 0) | (dparams ? ADST_GRAD_PARAMS : 0);
   const bool want_dk = dcoeff != nullptr;
   Checked c;
@@ -639,12 +638,17 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
     const hipError_t e = static_workspace(&ws);
     if (e != hipSuccess) return hip_fail(e, "static workspace");
     ws_bytes = kStaticWsBytes;
+    scratch_in = static_cast<char*>(ws) + L.total;
+    scratch_bytes = kStaticWsBytes - L.total;
   }
   if (ws_bytes < L.total || !ws)
     return fail(ADST_ERR_WORKSPACE, "adst_vjp needs " + std::to_string(L.total) +
                                         " workspace bytes, got " + std::to_string(ws_bytes));
   const uint64_t S = c.state_bytes;
+  uint64_t scratch_used;
+  void* const scratch = sweep_scratch(c, steps, scratch_in, scratch_bytes, &scratch_used);
   std::vector<Range> outs = {range_of("dx0", dx0, S), range_of("ws", ws, L.total)};
+  if (scratch) outs.push_back(range_of("scratch", scratch, scratch_used));
   if (dcoeff) outs.push_back(range_of("dcoeff", dcoeff, S));
   if (xT) outs.push_back(range_of("xT", xT, S));
   if (loss_dev) outs.push_back(range_of("loss_dev", loss_dev, sizeof(double)));
@@ -654,9 +658,6 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
   if (loss != ADST_LOSS_HALF_SQ) ins.push_back(range_of("loss_aux", loss_aux, S));
   st = check_disjoint(outs, ins);
   if (st != ADST_OK) return st;
-  std::vector<Range> arrays = ins;
-  arrays.insert(arrays.end(), outs.begin(), outs.end());
-  void* const scratch = sweep_scratch(c, steps, ws, L.total, ws_bytes, arrays);
   if (info) fill_info(c, plan, mem_budget_bytes, want_dk, loss, info);
   if (log_level() > 0) log_plan(c, plan, mem_budget_bytes, want_dk, loss);
 
@@ -849,6 +850,64 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
   return ADST_OK;
 }
 
+// adst_forward and adst_forward_scratch.
+adst_status forward_impl(const adst_problem* prob, const void* x0, const void* coeff,
+                         int32_t steps, void* xT, void* ws, uint64_t ws_bytes, void* scratch_in,
+                         uint64_t scratch_bytes, hipStream_t stream) {
+  Checked c;
+  adst_status st = check_problem(prob, 0, &c);
+  if (st != ADST_OK) return st;
+  if (steps < 0) return fail(ADST_ERR_ARG, "steps must be >= 0");
+  if (!x0 || !xT) return fail(ADST_ERR_ARG, "x0 and xT are required");
+  if (prob->kind == ADST_VARDIFF2D9 && !coeff)
+    return fail(ADST_ERR_ARG, "the variable-coefficient kind needs coeff (K)");
+  const uint64_t S = c.state_bytes;
+  const uint64_t need = (steps >= 2 && !c.in_place) ? S : 0;
+  if (ws_bytes < need || (need && !ws))
+    return fail(ADST_ERR_WORKSPACE, "adst_forward needs " + std::to_string(need) + " workspace bytes");
+  uint64_t scratch_used;
+  void* const scratch = sweep_scratch(c, steps, scratch_in, scratch_bytes, &scratch_used);
+  std::vector<Range> outs = {range_of("xT", xT, S)};
+  if (need) outs.push_back(range_of("ws", ws, need));
+  if (scratch) outs.push_back(range_of("scratch", scratch, scratch_used));
+  std::vector<Range> ins = {range_of("x0", x0, S)};
+  if (prob->kind == ADST_VARDIFF2D9) ins.push_back(range_of("coeff", coeff, S));
+  st = check_disjoint(outs, ins);
+  if (st != ADST_OK) return st;
+
+  hipError_t e;
+  if (steps == 0) {
+    e = launch_copy(xT, x0, (int64_t)S, stream);
+    if (e != hipSuccess) return hip_fail(e, "copy");
+    g_last_error.clear();
+    return ADST_OK;
+  }
+  if (c.in_place) {  // pipelined sweeps from x0 straight into xT
+    e = launch_gs_forward(c.shape, x0, xT, steps, scratch, stream);
+    if (e != hipSuccess) return hip_fail(e, "forward sweeps");
+    g_last_error.clear();
+    return ADST_OK;
+  }
+  // Launches of up to fuse_fwd steps each, the shorter remainder first;
+  // they alternate between xT and ws so that the last one writes xT.
+  const int32_t d = c.fuse_fwd;
+  const int32_t n_launch = (steps + d - 1) / d;
+  const void* cur = x0;
+  int32_t done = 0;
+  for (int32_t k = 0; k < n_launch; ++k) {
+    void* dst = ((n_launch - 1 - k) % 2 == 0) ? xT : ws;
+    const int32_t n = (k == 0 && steps % d != 0) ? steps % d : d;
+    e = n >= 2 ? launch_forward_n(c.shape, cur, coeff, dst, n, stream)
+               : launch_forward(c.shape, cur, coeff, dst, stream);
+    if (e != hipSuccess) return hip_fail(e, "forward step");
+    done += n;
+    cur = dst;
+  }
+  if (done != steps) return fail(ADST_ERR_ARG, "internal: forward launch count");
+  g_last_error.clear();
+  return ADST_OK;
+}
+
 }  // namespace
 }  // namespace adst
 
@@ -897,58 +956,13 @@ uint64_t adst_sweep_workspace_bytes(const adst_problem* prob, int32_t steps) {
 adst_status adst_forward(const adst_problem* prob, const void* x0, const void* coeff,
                          int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
                          hipStream_t stream) {
-  Checked c;
-  adst_status st = check_problem(prob, 0, &c);
-  if (st != ADST_OK) return st;
-  if (steps < 0) return fail(ADST_ERR_ARG, "steps must be >= 0");
-  if (!x0 || !xT) return fail(ADST_ERR_ARG, "x0 and xT are required");
-  if (prob->kind == ADST_VARDIFF2D9 && !coeff)
-    return fail(ADST_ERR_ARG, "the variable-coefficient kind needs coeff (K)");
-  const uint64_t S = c.state_bytes;
-  const uint64_t need = (steps >= 2 && !c.in_place) ? S : 0;
-  if (ws_bytes < need || (need && !ws))
-    return fail(ADST_ERR_WORKSPACE, "adst_forward needs " + std::to_string(need) + " workspace bytes");
-  std::vector<Range> outs = {range_of("xT", xT, S)};
-  if (need) outs.push_back(range_of("ws", ws, need));
-  std::vector<Range> ins = {range_of("x0", x0, S)};
-  if (prob->kind == ADST_VARDIFF2D9) ins.push_back(range_of("coeff", coeff, S));
-  st = check_disjoint(outs, ins);
-  if (st != ADST_OK) return st;
+  return forward_impl(prob, x0, coeff, steps, xT, ws, ws_bytes, nullptr, 0, stream);
+}
 
-  hipError_t e;
-  if (steps == 0) {
-    e = launch_copy(xT, x0, (int64_t)S, stream);
-    if (e != hipSuccess) return hip_fail(e, "copy");
-    g_last_error.clear();
-    return ADST_OK;
-  }
-  if (c.in_place) {  // pipelined sweeps from x0 straight into xT
-    std::vector<Range> arrays = ins;
-    arrays.insert(arrays.end(), outs.begin(), outs.end());
-    e = launch_gs_forward(c.shape, x0, xT, steps,
-                          sweep_scratch(c, steps, ws, 0, ws_bytes, arrays), stream);
-    if (e != hipSuccess) return hip_fail(e, "forward sweeps");
-    g_last_error.clear();
-    return ADST_OK;
-  }
-  // Launches of up to fuse_fwd steps each, the shorter remainder first;
-  // they alternate between xT and ws so that the last one writes xT.
-  const int32_t d = c.fuse_fwd;
-  const int32_t n_launch = (steps + d - 1) / d;
-  const void* cur = x0;
-  int32_t done = 0;
-  for (int32_t k = 0; k < n_launch; ++k) {
-    void* dst = ((n_launch - 1 - k) % 2 == 0) ? xT : ws;
-    const int32_t n = (k == 0 && steps % d != 0) ? steps % d : d;
-    e = n >= 2 ? launch_forward_n(c.shape, cur, coeff, dst, n, stream)
-               : launch_forward(c.shape, cur, coeff, dst, stream);
-    if (e != hipSuccess) return hip_fail(e, "forward step");
-    done += n;
-    cur = dst;
-  }
-  if (done != steps) return fail(ADST_ERR_ARG, "internal: forward launch count");
-  g_last_error.clear();
-  return ADST_OK;
+adst_status adst_forward_scratch(const adst_problem* prob, const void* x0, const void* coeff,
+                                 int32_t steps, void* xT, void* ws, uint64_t ws_bytes,
+                                 void* scratch, uint64_t scratch_bytes, hipStream_t stream) {
+  return forward_impl(prob, x0, coeff, steps, xT, ws, ws_bytes, scratch, scratch_bytes, stream);
 }
 
 adst_status adst_vjp(const adst_problem* prob, const void* x0, const void* coeff, int32_t steps,
@@ -956,7 +970,18 @@ adst_status adst_vjp(const adst_problem* prob, const void* x0, const void* coeff
                      void* dx0, void* dcoeff, void* xT, double* loss_dev, double* dparams,
                      void* ws, uint64_t ws_bytes, hipStream_t stream, adst_plan_info* info) {
   return vjp_impl(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx0, dcoeff,
-                  xT, loss_dev, dparams, ws, ws_bytes, false, stream, info);
+                  xT, loss_dev, dparams, ws, ws_bytes, nullptr, 0, false, stream, info);
+}
+
+adst_status adst_vjp_scratch(const adst_problem* prob, const void* x0, const void* coeff,
+                             int32_t steps, int32_t loss, const void* loss_aux,
+                             uint64_t mem_budget_bytes, int32_t sched, void* dx0, void* dcoeff,
+                             void* xT, double* loss_dev, double* dparams, void* ws,
+                             uint64_t ws_bytes, void* scratch, uint64_t scratch_bytes,
+                             hipStream_t stream, adst_plan_info* info) {
+  return vjp_impl(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx0, dcoeff,
+                  xT, loss_dev, dparams, ws, ws_bytes, scratch, scratch_bytes, false, stream,
+                  info);
 }
 
 adst_status adst_vjp_static_ws(const adst_problem* prob, const void* x0, const void* coeff,
@@ -965,7 +990,7 @@ adst_status adst_vjp_static_ws(const adst_problem* prob, const void* x0, const v
                                void* xT, double* loss_dev, double* dparams, hipStream_t stream,
                                adst_plan_info* info) {
   return vjp_impl(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx0, dcoeff,
-                  xT, loss_dev, dparams, nullptr, 0, true, stream, info);
+                  xT, loss_dev, dparams, nullptr, 0, nullptr, 0, true, stream, info);
 }
 
 adst_status adst_ilp_solve(const adst_ilp_array* arrays, int32_t n_arrays,

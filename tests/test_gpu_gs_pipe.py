@@ -1,6 +1,6 @@
-"""The persistent launch of the in-place kind's sweeps (a workspace with
-adst_sweep_workspace_bytes more than the plan's) against the oracle and
-against the level launches (the plan's own workspace), bit for bit.
+"""The persistent launch of the in-place kind's sweeps (calls with
+adst_sweep_workspace_bytes of scratch) against the oracle and against the
+level launches (calls without), bit for bit.
 
 Shapes sit at the edges of the launch's pieces: strips of 128 (f64) or 256
 (f32) columns that move one column per sweep, groups of 8 or 16 sweeps (four
@@ -29,23 +29,23 @@ def _gpu():
     adst.lib()
 
 
-def run(dtype, x, aux, T, room, tail=None):
-    """adst_vjp in a workspace of the plan's bytes and `room` more; `tail`
-    (optional) is placed where the scratch would be and read as loss_aux."""
+def run(dtype, x, aux, T, room):
+    """adst_vjp_scratch with `room` bytes of scratch; without any, adst_vjp in
+    a workspace larger than the plan's, whose tail it leaves alone."""
     import torch
     shape = x.shape
     prob = adst.make_problem(GS, dtype, (shape[1], shape[0], 1))
     need = adst.adst_plan(prob, T, 0, adst.ADST_SCHED_AUTO).workspace_bytes
-    ws = torch.full((need + room,), 0x5a, dtype=torch.uint8, device="cuda")
+    spare = room or adst.adst_sweep_workspace_bytes(prob, T)
+    ws = torch.full((need + spare,), 0x5a, dtype=torch.uint8, device="cuda")
+    scratch = torch.full((room,), 0x5a, dtype=torch.uint8, device="cuda") if room else None
     x0, g = dev(x), dev(aux)
-    if tail is not None:
-        g = ws[need:need + g.numel() * g.element_size()].view(g.dtype).view(shape)
-        g.copy_(dev(tail))
     dx0, xT = torch.empty_like(x0), torch.empty_like(x0)
     L = torch.empty((), dtype=torch.float64, device="cuda")
     adst.adst_vjp(prob, x0, None, T, SEED, g, 0, adst.ADST_SCHED_AUTO, dx0, None, xT, L, None, ws,
-                  need + room)
+                  need + spare, scratch=scratch, scratch_bytes=room)
     torch.cuda.synchronize()
+    assert bool((ws[need:] == 0x5a).all())
     return dx0.cpu().numpy(), xT.cpu().numpy(), float(L)
 
 
@@ -82,14 +82,50 @@ def test_values_that_are_not_finite():
         assert np.array_equal(a[k], b[k], equal_nan=True)
 
 
-def test_scratch_that_overlaps_an_array_is_not_used():
-    """A larger ws_bytes whose part beyond the plan's holds loss_aux."""
+def test_forward_leaves_a_workspace_it_does_not_need():
+    """In this kind's forward call ws is not used at all, however large."""
+    import torch
     r = np.random.Generator(np.random.PCG64(23))
-    x, aux = r.uniform(-1, 1, (50, 300)), r.standard_normal((50, 300))
+    x = r.uniform(-1, 1, (50, 300))
     prob = adst.make_problem(GS, F64, (300, 50, 1))
-    room = max(adst.adst_sweep_workspace_bytes(prob, 9), aux.nbytes)
-    a, b = run(F64, x, aux, 9, room, tail=aux), run(F64, x, aux, 9, 0)
-    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2] == b[2]
+    room = adst.adst_sweep_workspace_bytes(prob, 9)
+    x0, ref = dev(x), oracle.forward(GS, x, steps=9)
+    for scratch in (None, torch.full((room,), 0x5a, dtype=torch.uint8, device="cuda")):
+        ws = torch.full((2 * room,), 0x5a, dtype=torch.uint8, device="cuda")
+        xT = torch.empty_like(x0)
+        adst.adst_forward(prob, x0, None, 9, xT, ws, ws.numel(), scratch=scratch,
+                          scratch_bytes=0 if scratch is None else room)
+        assert bool((ws == 0x5a).all())
+        assert np.array_equal(xT.cpu().numpy(), ref)
+
+
+def test_the_callers_workspace_and_scratch_are_the_ones_used():
+    """A call takes no workspace of its own beside a given one, and beyond the
+    outputs only the scratch, which the caller can give or decline."""
+    import torch
+    r = np.random.Generator(np.random.PCG64(25))
+    x = dev(r.uniform(-1, 1, (300, 500)))
+    T, budget, flags = 12, 10 * x.nbytes, adst.ADST_FORCE_TAPE
+    prob = adst.make_problem(GS, F64, (500, 300, 1), flags=flags)
+    extra = adst.adst_sweep_workspace_bytes(prob, T)
+    need = adst.adst_plan(prob, T, budget, adst.ADST_SCHED_BINOMIAL).workspace_bytes
+    assert need > 10 * x.nbytes > extra > 0
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    mine = torch.empty(extra, dtype=torch.uint8, device="cuda")
+    ref = oracle.forward(GS, x.cpu().numpy(), steps=T)
+    for scratch, used in ((None, extra), (mine, extra), (False, 0)):
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        out = adst.vjp(GS, x, None, T, budget_bytes=budget, sched=adst.ADST_SCHED_BINOMIAL,
+                       flags=flags, ws=ws, scratch=scratch)
+        torch.cuda.synchronize()
+        taken = torch.cuda.max_memory_allocated() - before
+        assert out["ws"] is ws and out["scratch_bytes"] == used
+        assert taken <= 2 * x.nbytes + (extra if scratch is None else 0) + 4096, taken
+        assert np.array_equal(out["xT"].cpu().numpy(), ref)
+        del out
+        assert np.array_equal(adst.forward(GS, x, None, T, scratch=scratch).cpu().numpy(), ref)
 
 
 def test_both_python_calls_on_another_stream():

@@ -63,3 +63,37 @@ def test_scratch_is_bounded_and_of_the_documented_size():
         for n in (4096, 20_000):
             share = scratch(dtype, n, n, 100) / (n * n * isz)
             assert 0 < share <= (0.28 if dtype == F64 else 0.14)
+
+
+def test_scratch_that_overlaps_an_array_is_refused():
+    """Only the bytes that the sweeps would use count; with too little the
+    scratch is not used, so another argument's error is what the call reports.
+    The pointers are never dereferenced."""
+    import torch
+    if torch.cuda.device_count() > 0:
+        pytest.skip("host-only argument checks")
+    prob = adst.make_problem(GS, F64, (300, 50, 1))
+    S, T = 300 * 50 * 8, 9
+    need = adst.adst_sweep_workspace_bytes(prob, T)
+    x0, aux, dx0, xT, L, ws, free = (0x10000000 * (i + 1) for i in range(7))
+
+    def status(at, nbytes, **kw):
+        a = dict(xT=xT, steps=T)
+        a.update(kw)
+        with pytest.raises(adst.AdstError) as e:
+            adst.adst_vjp(prob, x0, None, a["steps"], adst.ADST_LOSS_SEED, aux, 0, 0, dx0, None,
+                          a["xT"], L, None, ws, 1 << 20, 0, scratch=at, scratch_bytes=nbytes)
+        return e.value.status, str(e.value)
+
+    for name, at in (("x0", x0), ("loss_aux", aux), ("dx0", dx0), ("xT", xT), ("ws", ws)):
+        for p in (at, at - need // 2):
+            st, msg = status(p, need)
+            assert st == adst.ADST_ERR_ARG and "scratch" in msg and name in msg
+        if name in ("x0", "xT"):
+            with pytest.raises(adst.AdstError, match="scratch"):
+                adst.adst_forward(prob, x0, None, T, xT, None, 0, 0, scratch=at,
+                                  scratch_bytes=need)
+    # too little, or beside the arrays: the next error is the one reported
+    for at, nbytes in ((x0, need // 2), (free, need)):
+        st, msg = status(at, nbytes, xT=dx0)
+        assert st == adst.ADST_ERR_ARG and "scratch" not in msg
