@@ -223,7 +223,9 @@ typedef struct {
   int64_t fwd_launches;     /* forward actions (a fused or a pipelined run counts once) */
   int64_t adj_launches;     /* adjoint actions (likewise) */
   int64_t fwd_kernels;      /* forward kernel dispatches the actions enqueue (the in-place kind:
-                               wavefront levels, one dispatch each in level launches) */
+                               one per wavefront level, as adst_vjp enqueues them and adst_plan
+                               reports; with scratch one per 256 sweeps, beside the fill that
+                               clears its progress counters) */
   int64_t adj_kernels;      /* adjoint kernel dispatches the actions enqueue (likewise) */
   uint64_t state_bytes;     /* bytes of one state */
   uint64_t budget_bytes;    /* the budget passed in */
@@ -442,7 +444,7 @@ typedef struct {
   int32_t phase;          /* 0 forward sweep, 1 recomputation, 2 adjoint, 3 loss and seed,
                              4 the constants' final sum (the phase of its first launch) */
   int32_t reserved;
-  int64_t launches;       /* kernel dispatches (the in-place kind: wavefront levels) */
+  int64_t launches;       /* kernel dispatches (as fwd_kernels and adj_kernels count them) */
   double ms_sum;          /* summed duration (ms) */
   double ms_min, ms_max;  /* per dispatch (a pipelined sequence: its average dispatch) */
   double alg_bytes_sum;   /* algorithmic bytes of all those dispatches */

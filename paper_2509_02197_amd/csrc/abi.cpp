@@ -310,8 +310,19 @@ bool seed_in_aux(const Checked& c, int32_t loss, int32_t steps) {
          !(c.shape.limit && !adjoint_applies_limit(c.shape, c.want_dp));
 }
 
+// Launches and bytes of one action of the in-place kind: of its persistent
+// launches where the call has the scratch for them, else of its levels, which
+// read and write each point once per sweep.
+GsPipeCost in_place_cost(const Checked& c, const PerPoint& pp, const adst_action& a, bool scratch) {
+  const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
+  if (scratch) return gs_pipe_cost(c.shape, adj, a.n);
+  return {gs_kernel_launches(c.shape, adj, a.n),
+          uint64_t(c.npoints) * uint64_t(a.n) * (adj ? pp.adj : pp.fwd)};
+}
+
+// scratch: an in-place call that has the scratch of the persistent launches.
 void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk, int32_t loss,
-               adst_plan_info* info) {
+               bool scratch, adst_plan_info* info) {
   const Layout L = layout_for(c, plan);
   const PerPoint pp = per_point_bytes(c, want_dk, loss);
   const uint64_t sb = seed_in_aux(c, loss, plan.steps) ? 2 * itemsize(c.shape.dtype) : pp.seed;
@@ -333,7 +344,7 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
     const bool adj_op = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJ2 || a.op == ADST_OP_ADJW;
     if (!fwd_op && !adj_op) continue;
     if (fused_fwd_adj(c, plan.acts, i)) continue;  // counted with its adjoint
-    const int64_t k = c.in_place ? gs_kernel_launches(c.shape, adj_op, a.n) : 1;
+    const int64_t k = c.in_place ? in_place_cost(c, pp, a, scratch).launches : 1;
     (fwd_op ? info->fwd_kernels : info->adj_kernels) += k;
     i += paired_adj(c, plan.acts, i) ? 1 : stored_run(c, plan.acts, i) - 1;
   }
@@ -343,13 +354,17 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
   info->workspace_bytes = L.total;
   info->fwd_workspace_bytes = (plan.steps >= 2 && !c.in_place) ? c.state_bytes : 0;
   // A fused launch moves its inputs and outputs once for its n steps (a
-  // store-through run writes each of its n states); a pipelined run of the
-  // in-place kind is counted as its n steps.
+  // store-through run writes each of its n states).
   const uint64_t n = uint64_t(c.npoints);
-  uint64_t per_point = sb, fwd_per_point = 0;
+  uint64_t per_point = sb, fwd_per_point = 0, in_place_fwd = 0, in_place_adj = 0;
   bool first_adj = true;
   for (size_t i = 0; i < plan.acts.size(); ++i) {
     const adst_action& a = plan.acts[i];
+    if (c.in_place && a.op != ADST_OP_SEED) {
+      const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
+      (adj ? in_place_adj : in_place_fwd) += in_place_cost(c, pp, a, scratch).bytes;
+      continue;
+    }
     switch (a.op) {
       case ADST_OP_FWD: {
         if (fused_fwd_adj(c, plan.acts, i)) break;  // moves the adjoint's bytes only
@@ -362,9 +377,6 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
         if (fused_fwd_adj(c, plan.acts, i)) break;  // moves the adjoint's bytes only
         fwd_per_point += fb;
         break;
-      case ADST_OP_FWDW:
-        fwd_per_point += uint64_t(a.n) * fb;
-        break;
       case ADST_OP_ADJ:
       case ADST_OP_ADJ2:
         per_point += (first_adj ? ab1 : ab) + db;
@@ -374,16 +386,12 @@ void fill_info(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk
           ++i;
         }
         break;
-      case ADST_OP_ADJW:
-        per_point += uint64_t(a.n) * ab;
-        first_adj = false;
-        break;
       default:
         break;
     }
   }
-  info->alg_bytes = n * (per_point + fwd_per_point);
-  info->fwd_alg_bytes = n * fwd_per_point;
+  info->fwd_alg_bytes = n * fwd_per_point + in_place_fwd;
+  info->alg_bytes = n * per_point + info->fwd_alg_bytes + in_place_adj;
 }
 
 // ADST_LOG=1 in the environment prints each adst_vjp call's plan to
@@ -396,12 +404,13 @@ int log_level() {
   return level;
 }
 
-void log_plan(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk, int32_t loss) {
+void log_plan(const Checked& c, const Plan& plan, uint64_t budget, bool want_dk, int32_t loss,
+              bool scratch) {
   static const char* const kSched[4] = {"auto", "store_all", "uniform", "binomial"};
   static const char* const kKind[4] = {"jacobi2d5", "allencahn3d7", "vardiff2d9",
                                        "gaussseidel2d5"};
   adst_plan_info info;
-  fill_info(c, plan, budget, want_dk, loss, &info);
+  fill_info(c, plan, budget, want_dk, loss, scratch, &info);
   std::fprintf(stderr,
                "adst plan: %s %s %dx%dx%d T=%d budget=%llu B sched=%s slots=%d (c=%d) "
                "needs_state=%d fwd_steps=%lld (recompute %lld) adj_steps=%lld "
@@ -658,8 +667,8 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
   if (loss != ADST_LOSS_HALF_SQ) ins.push_back(range_of("loss_aux", loss_aux, S));
   st = check_disjoint(outs, ins);
   if (st != ADST_OK) return st;
-  if (info) fill_info(c, plan, mem_budget_bytes, want_dk, loss, info);
-  if (log_level() > 0) log_plan(c, plan, mem_budget_bytes, want_dk, loss);
+  if (info) fill_info(c, plan, mem_budget_bytes, want_dk, loss, scratch != nullptr, info);
+  if (log_level() > 0) log_plan(c, plan, mem_budget_bytes, want_dk, loss, scratch != nullptr);
 
   // ---- interpret the plan
   // The adjoint ping-pongs between dx0 and the workspace buffer G, one swap
@@ -719,14 +728,15 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
     if (c.in_place && a.op != ADST_OP_SEED) {
       const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
       if (!adj && a.op != ADST_OP_FWD && a.op != ADST_OP_FWDW) return hip_fail(hipErrorInvalidValue, "plan");
+      const GsPipeCost cost = in_place_cost(c, pp, a, scratch != nullptr);
       e = traced(cat, scratch ? (adj ? "gs_pipe<adj>" : "gs_pipe<fwd>") : kernel_label(c, a, 1, false),
-                 npts * double(a.n) * double(adj ? pp.adj : pp.fwd),
+                 double(cost.bytes),
                  [&] {
                    return adj ? launch_gs_adjoint(c.shape, dx0, a.n, scratch, stream)
                               : launch_gs_forward(c.shape, buffer(a.src), buffer(a.dst), a.n,
                                                   scratch, stream);
                  },
-                 gs_kernel_launches(c.shape, adj, a.n));
+                 cost.launches);
       if (e != hipSuccess) return hip_fail(e, "kernel launch");
       continue;
     }
@@ -922,7 +932,7 @@ adst_status adst_plan(const adst_problem* prob, int32_t steps, uint64_t mem_budg
   Plan plan;
   adst_status st = make_plan(prob, steps, mem_budget_bytes, sched, grads, &c, &plan);
   if (st != ADST_OK) return st;
-  fill_info(c, plan, mem_budget_bytes, c.want_dk, ADST_LOSS_HALF_SQ, out);
+  fill_info(c, plan, mem_budget_bytes, c.want_dk, ADST_LOSS_HALF_SQ, false, out);
   g_last_error.clear();
   return ADST_OK;
 }

@@ -172,6 +172,19 @@ uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps) {
   return bytes <= gp_most_bytes(s) ? bytes : 0;
 }
 
+GsPipeCost gs_pipe_cost(const StepShape& s, bool adjoint, int32_t sweeps) {
+  GsPipeCost c;
+  const int64_t isz = s.dtype == ADST_F64 ? 8 : 4, phases = int64_t(sweeps) + (adjoint ? 1 : 0);
+  for (int64_t ph = 0; ph < phases; ph += kGpMaxPhases) {
+    const int n = (int)std::min<int64_t>(kGpMaxPhases, phases - ph), nw = gp_waves(s, n);
+    const GpGeom g = gp_geom(s, n, nw);
+    ++c.launches;
+    // the state in and out per group; the halo's values written and read once
+    c.bytes += 2 * isz * s.ny * (uint64_t(g.ngroups) * s.nx + uint64_t(n) * (g.ncol - 1));
+  }
+  return c;
+}
+
 hipError_t gs_pipe_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
                            void* scratch, hipStream_t st) {
   if (s.dtype == ADST_F64)

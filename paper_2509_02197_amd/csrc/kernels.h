@@ -152,6 +152,12 @@ hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, void* 
                              hipStream_t stream);
 int64_t gs_kernel_launches(const StepShape& s, bool adjoint, int32_t sweeps);
 uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps);
+// The persistent launches of such a run, and the bytes they have to move.
+struct GsPipeCost {
+  int64_t launches = 0;
+  uint64_t bytes = 0;
+};
+GsPipeCost gs_pipe_cost(const StepShape& s, bool adjoint, int32_t sweeps);
 hipError_t gs_pipe_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
                            void* scratch, hipStream_t stream);
 hipError_t gs_pipe_adjoint(const StepShape& s, void* g, int32_t sweeps, void* scratch,

@@ -136,13 +136,32 @@ def test_zero_steps():
     assert np.array_equal(g["xT"], inp["x0"])
 
 
-def test_trace_and_kernel_counts():
+@pytest.mark.parametrize("T", [9, 300])
+def test_trace_and_kernel_counts(T):
+    """One persistent launch per 256 phases with the scratch, one launch per
+    wavefront level without, under the kernel's own name and with the bytes
+    that it moves: at least the state in and out once, and less than that for
+    every sweep where several share a pass."""
     inp = inputs(F64, (200, 300), 6)
-    g = gpu_vjp(GS, inp, 9, HALF_SQ, flags=adst.ADST_TRACE)
-    info = g["info"]
-    assert info["ms_fwd_sweep"] > 0 and info["ms_adj"] > 0 and info["ms_seed"] > 0
-    assert info["fwd_kernels"] > 9 and info["adj_kernels"] > info["fwd_kernels"]
-    check(F64, inp, 9, HALF_SQ, g)
+    npts, per_step = 200 * 300, 16
+    for scratch in (None, False):
+        g = gpu_vjp(GS, inp, T, HALF_SQ, flags=adst.ADST_TRACE, scratch=scratch)
+        info, ks = g["info"], {k["name"]: k for k in adst.adst_trace_kernels()}
+        assert info["ms_fwd_sweep"] > 0 and info["ms_adj"] > 0 and info["ms_seed"] > 0
+        base = "gs_wave" if scratch is False else "gs_pipe"
+        assert {k for k in ks if k.startswith("gs_")} == {base + "<fwd>", base + "<adj>"}
+        fwd, adj = ks[base + "<fwd>"], ks[base + "<adj>"]
+        assert (fwd["launches"], adj["launches"]) == (info["fwd_kernels"], info["adj_kernels"])
+        assert fwd["alg_bytes_sum"] == info["fwd_alg_bytes"]
+        if scratch is False:
+            assert info["fwd_kernels"] > T and info["adj_kernels"] > info["fwd_kernels"]
+            assert fwd["alg_bytes_sum"] == adj["alg_bytes_sum"] == npts * T * per_step
+        else:
+            assert info["fwd_kernels"] == -(-T // 256) and info["adj_kernels"] == -(-(T + 1) // 256)
+            for k, phases in ((fwd, T), (adj, T + 1)):
+                groups = -(-phases // 8)
+                assert npts * per_step * groups / 2 <= k["alg_bytes_sum"] < npts * per_step * phases / 2
+        check(F64, inp, T, HALF_SQ, g)
 
 
 def test_repeat_calls_same_bits():
