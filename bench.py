@@ -521,8 +521,6 @@ def rocprof_label(name):
     if base == "fwd_allencahn3d7_n":   # <R, K, RPT, (NZ,) NT, ST, ...>
         nt_st = [a for a in targs if a in ("true", "false")]
         return f"fwd_allencahn3d7_n<{targs[1]}" + (",store>" if nt_st[1] == "true" else ">")
-    if base == "fwd_vardiff2d9_x2":    # <R, TR, NT, ST>
-        return "fwd_vardiff2d9_x2" + ("<store>" if t(3) else "")
     if base == "jacobi_march":         # <R, K, ADJ, VEC, LIM, ST, ...>
         return (f"jacobi_march<{'adj' if t(2) else 'fwd'},{targs[1]}" +
                 (",lim" if len(targs) > 4 and t(4) else "") +
@@ -533,10 +531,11 @@ def rocprof_label(name):
         return base + ("<dp>" if t(2) else "")
     if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>
         return base + ("<adj>" if t(1) else "<fwd>")
-    if base == "ac_march":             # <R, NF, ADJ, RR, ZC, DA, ST, NT>
+    if base == "ac_march":             # <R, NF, ADJ, RR, DA, ST, NT, MW>
         if t(2):
             return "ac_march<adj>" if targs[1] == "0" else f"ac_march<fwd{targs[1]}+adj>"
-        return f"ac_march<fwd,{targs[1]}" + (",store>" if t(6) else ">")
+        stores = [a for a in targs if a in ("true", "false")][1]
+        return f"ac_march<fwd,{targs[1]}" + (",store>" if stores == "true" else ">")
     if base == "adj_allencahn3d7":     # <R, DP, NT>
         return "adj_allencahn3d7<dp>" if t(1) else "adj_allencahn3d7"
     if base == "adj_vardiff2d9":       # <R, WANT_DK, TR, DP, NT>

@@ -733,7 +733,7 @@ __device__ inline float zero_outside(float v, uint64_t m) {
 template <int N>
 using IC = std::integral_constant<int, N>;
 
-template <class R, int NF, bool ADJ, int RR, int ZC, int DA, bool ST, bool NT, int MW>
+template <class R, int NF, bool ADJ, int RR, int DA, bool ST, bool NT, int MW>
 __global__ __launch_bounds__(kBX * MW) void ac_march(AcMarchArgs<R> a) {
   using M = AcMarch<NF, RR, MW>;
   constexpr int H = M::H, SY = M::SY;
@@ -756,7 +756,7 @@ __global__ __launch_bounds__(kBX * MW) void ac_march(AcMarchArgs<R> a) {
   const int lane = (int)threadIdx.x, w = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
   const int c = bx * M::OX - H + lane;      // this lane's column
   const int jw = by * M::OY - H + w * RR;   // this wave's first row
-  const int zc = min(a.zc, ZC), z0 = bz * zc, z1 = min(z0 + zc, a.nz);
+  const int zc = a.zc, z0 = bz * zc, z1 = min(z0 + zc, a.nz);
   const int nx = a.nx, ny = a.ny, nz = a.nz, plane = nx * ny;
   const bool cin = c >= 0 && c < nx;
   // the lanes at the region's sides read the column beyond it (ring), the
@@ -1043,19 +1043,18 @@ hipError_t march(const StepShape& s, const R* x, const R* g, R* y, R* m0, R* m1,
     if (int64_t(s.nx) * s.ny * int64_t(sizeof(R)) >= kTallPlaneBytes)
       return march<R, NF, ADJ, ST, RR, kTallAdjWaves>(s, x, g, y, m0, m1, st);
   }
-  constexpr int ZC = kMarchPlanes;  // most planes of a chunk
   using M = AcMarch<NF, RR, MW>;
   const int tx = cdiv(s.nx, M::OX), ty = cdiv(s.ny, M::OY);
-  const int zc = z_chunk(tx * int64_t(ty), s.nz, ZC, MW == kMW ? kWant4 : kWant16);
+  const int zc = z_chunk(tx * int64_t(ty), s.nz, kMarchPlanes, MW == kMW ? kWant4 : kWant16);
   const int nt = tx * ty * cdiv(s.nz, zc);
   const R D = R(s.p0), C = R(s.p1);
   const AcMarchArgs<R> a{x, g, y, m0, m1, s.nx, s.ny, s.nz, tx, ty, nt, zc,
                          D, C, R(1) + D * R(-6), R(3) * C};
   const dim3 grid(xcd_grid(nt)), block(kBX, MW);
   if (streams(s))
-    ac_march<R, NF, ADJ, RR, ZC, kMarchAhead, ST, true, MW><<<grid, block, 0, st>>>(a);
+    ac_march<R, NF, ADJ, RR, kMarchAhead, ST, true, MW><<<grid, block, 0, st>>>(a);
   else
-    ac_march<R, NF, ADJ, RR, ZC, kMarchAhead, ST, false, MW><<<grid, block, 0, st>>>(a);
+    ac_march<R, NF, ADJ, RR, kMarchAhead, ST, false, MW><<<grid, block, 0, st>>>(a);
   return hipGetLastError();
 }
 

@@ -55,8 +55,6 @@ def test_median_interval_empirical_coverage():
      "jacobi_march<fwd,4>"),
     ("void adst::(anonymous namespace)::adj_vardiff2d9<float, true, 4, false, true>(float)",
      "adj_vardiff2d9<dK>"),
-    ("void adst::(anonymous namespace)::fwd_vardiff2d9_x2<float, 8, true, true>(float)",
-     "fwd_vardiff2d9_x2<store>"),
     ("void adst::(anonymous namespace)::gs_wave<double, true, true>(double*)", "gs_wave<adj>"),
     ("void adst::(anonymous namespace)::seed_loss<double, 1>(double const*)", "seed_loss"),
     ("__amd_rocclr_copyBuffer", "hipMemcpyAsync copy"),
@@ -79,6 +77,8 @@ def test_rocprof_names_map_to_library_labels(name, label):
     ("jacobi_pair_adjoint<float, false, true>(x)", "jacobi_pair_adjoint<dp>"),
     ("vd_march<double, true, true, false>(x)", "vd_march<store>"),
     ("gs_pipe<double, true, 8>(x)", "gs_pipe<adj>"),
+    ("ac_march<double, 3, false, 4, 1, true, false, 4>(x)", "ac_march<fwd,3,store>"),
+    ("ac_march<double, 0, true, 4, 1, false, true, 8>(x)", "ac_march<adj>"),
 ])
 def test_labels_of_kernels_with_run_time_chunks(name, label):
     assert bench.rocprof_label("void adst::(anonymous namespace)::" + name) == label
