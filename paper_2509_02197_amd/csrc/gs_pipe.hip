@@ -77,11 +77,17 @@ namespace {
 constexpr int kGpMaxPhases = 256;
 
 // Waves of a workgroup: eight, or four where that still gives every
-// workgroup of the launch a CU of its own (one fits a CU by its LDS). Half
+// workgroup at work at once a CU of its own (one fits a CU by its LDS). Half
 // the phases a group make a clock half as long on the CU, which shortens
 // the chain of a small grid (400 x 400 f64, T = 100: 1.26 -> 1.08 ms), but
-// twice the groups; with more of them than CUs the chip is short of places
-// (4096 x 4096: 6.7 ms with eight waves, 8.7 with four).
+// twice the groups; with more of them at work than CUs the chip is short of
+// places (4096 x 4096: 6.7 ms with eight waves, 8.7 with four). A strip starts
+// 88 clocks after its left neighbour and works for about ny + 112, so a group
+// has a few strips at work at a time. With all its strips counted, wide
+// grids of few rows took eight waves (reverse sweeps, eight, four, level
+// launches: 64 x 20000 f64, T = 10, 9.2, 6.3, 6.9 ms; 300 x 100000 f32, T = 20,
+// 25.5, 19.9, 24.6; 48 x 5000 f64, T = 100, 2.85, 2.01, 5.70); 33 shapes of 48
+// to 4000 rows, T = 8 to 200, in both types: none slower.
 constexpr int kGpWide = 8, kGpNarrow = 4, kGpCus = 256;
 
 struct GpGeom {
@@ -106,7 +112,8 @@ GpGeom gp_geom(const StepShape& s, int nph, int nwaves) {
 
 int gp_waves(const StepShape& s, int nph) {
   const GpGeom g = gp_geom(s, nph, kGpNarrow);
-  return g.ngroups * g.ncol <= kGpCus ? kGpNarrow : kGpWide;
+  const int64_t at_work = std::min<int64_t>(g.ncol, (int64_t(s.ny) + 112) / 88 + 2);
+  return g.ngroups * at_work <= kGpCus ? kGpNarrow : kGpWide;
 }
 
 // Whether launches of up to kGpMaxPhases phases can run the shape; where not,

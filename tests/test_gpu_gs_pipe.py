@@ -4,8 +4,8 @@ level launches (calls without), bit for bit.
 
 Shapes sit at the edges of the launch's pieces: strips of 128 (f64) or 256
 (f32) columns that move one column per sweep, groups of 8 or 16 sweeps (four
-or eight waves; the last grid has more than 256 workgroups of four, so takes
-eight), 256 sweeps per launch, odd rows, grids without interior points.
+or eight waves: EIGHT), 256 sweeps per launch, odd rows, grids without interior
+points.
 """
 import numpy as np
 import pytest
@@ -55,7 +55,13 @@ CASES = [(F64, (70, 127), 7), (F64, (9, 128), 8), (F64, (200, 129), 9), (F64, (1
          (F32, (20, 259), 130), (F64, (21, 5001), 60)]
 
 
-@pytest.mark.parametrize("dtype,shape,T", CASES)
+# More than 256 workgroups of four waves would be at work at once, so eight
+# waves are taken (twice the phases a group, and twice the halo): rows enough
+# for the interior form, several strips and halo slots used more than once.
+EIGHT = [(F64, (510, 1210), 250), (F32, (515, 2403), 250)]
+
+
+@pytest.mark.parametrize("dtype,shape,T", CASES + EIGHT)
 def test_one_launch_gives_the_level_launches_bits(dtype, shape, T):
     say(f"gs pipe dtype={dtype} shape={shape} T={T}")
     r = np.random.Generator(np.random.PCG64(21))
@@ -64,6 +70,8 @@ def test_one_launch_gives_the_level_launches_bits(dtype, shape, T):
     prob = adst.make_problem(GS, dtype, (shape[1], shape[0], 1))
     room = adst.adst_sweep_workspace_bytes(prob, T)
     assert room > 0
+    if (dtype, shape, T) in EIGHT:  # four waves' halo: an eighth and a sixteenth of a state
+        assert room > 1.5 * x.nbytes * (1 / 8 if dtype == F64 else 1 / 16)
     a, b = run(dtype, x, aux, T, room), run(dtype, x, aux, T, 0)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2] == b[2]
     dx0, _, xT, L = oracle.vjp(GS, x, steps=T, loss=SEED, aux=aux)

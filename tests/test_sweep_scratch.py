@@ -65,6 +65,16 @@ def test_scratch_is_bounded_and_of_the_documented_size():
             assert 0 < share <= (0.28 if dtype == F64 else 0.14)
 
 
+def test_wide_grids_of_few_rows_take_the_narrow_workgroup():
+    """Few strips of a group are at work at a time there: the halo is that of
+    four waves, an eighth of an f64 state, not of eight."""
+    for nx, ny, T, eight in [(20_000, 64, 10, False), (5000, 48, 100, False),
+                             (100_000, 300, 20, False), (4096, 4096, 100, True),
+                             (5000, 3000, 100, True)]:
+        share = scratch(F64, nx, ny, T) / (nx * ny * 8)
+        assert (0.2 < share < 0.3) if eight else (0.1 < share < 0.2), (nx, ny, T)
+
+
 def test_scratch_that_overlaps_an_array_is_refused():
     """Only the bytes that the sweeps would use count; with too little the
     scratch is not used, so another argument's error is what the call reports.
