@@ -311,11 +311,11 @@ bool seed_in_aux(const Checked& c, int32_t loss, int32_t steps) {
 }
 
 // Launches and bytes of one action of the in-place kind: of its persistent
-// launches where the call has the scratch for them, else of its levels, which
-// read and write each point once per sweep.
+// launches where the call has the scratch for them and they are the faster,
+// else of its levels, which read and write each point once per sweep.
 GsPipeCost in_place_cost(const Checked& c, const PerPoint& pp, const adst_action& a, bool scratch) {
   const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
-  if (scratch) return gs_pipe_cost(c.shape, adj, a.n);
+  if (scratch && gs_takes_pipe(c.shape, adj, a.n)) return gs_pipe_cost(c.shape, adj, a.n);
   return {gs_kernel_launches(c.shape, adj, a.n),
           uint64_t(c.npoints) * uint64_t(a.n) * (adj ? pp.adj : pp.fwd)};
 }
@@ -729,7 +729,8 @@ adst_status vjp_impl(const adst_problem* prob, const void* x0, const void* coeff
       const bool adj = a.op == ADST_OP_ADJ || a.op == ADST_OP_ADJW;
       if (!adj && a.op != ADST_OP_FWD && a.op != ADST_OP_FWDW) return hip_fail(hipErrorInvalidValue, "plan");
       const GsPipeCost cost = in_place_cost(c, pp, a, scratch != nullptr);
-      e = traced(cat, scratch ? (adj ? "gs_pipe<adj>" : "gs_pipe<fwd>") : kernel_label(c, a, 1, false),
+      const bool pipe = scratch && gs_takes_pipe(c.shape, adj, a.n);
+      e = traced(cat, pipe ? (adj ? "gs_pipe<adj>" : "gs_pipe<fwd>") : kernel_label(c, a, 1, false),
                  double(cost.bytes),
                  [&] {
                    return adj ? launch_gs_adjoint(c.shape, dx0, a.n, scratch, stream)

@@ -380,7 +380,8 @@ int64_t gs_kernel_launches(const StepShape& s, bool adjoint, int32_t sweeps) {
 hipError_t launch_gs_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
                              void* scratch, hipStream_t stream) {
   if (sweeps <= 0) return hipErrorInvalidValue;
-  if (scratch) return gs_pipe_forward(s, src, dst, sweeps, scratch, stream);
+  if (scratch && gs_takes_pipe(s, false, sweeps))
+    return gs_pipe_forward(s, src, dst, sweeps, scratch, stream);
   if (s.dtype == ADST_F64)
     return gs_run<double, false>(s, static_cast<double*>(dst), static_cast<const double*>(src),
                                  sweeps, stream);
@@ -391,7 +392,8 @@ hipError_t launch_gs_forward(const StepShape& s, const void* src, void* dst, int
 hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, void* scratch,
                              hipStream_t stream) {
   if (sweeps <= 0) return hipErrorInvalidValue;
-  if (scratch) return gs_pipe_adjoint(s, g, sweeps, scratch, stream);
+  if (scratch && gs_takes_pipe(s, true, sweeps))
+    return gs_pipe_adjoint(s, g, sweeps, scratch, stream);
   if (s.dtype == ADST_F64)
     return gs_run<double, true>(s, static_cast<double*>(g), static_cast<const double*>(g),
                                 sweeps + 1, stream);

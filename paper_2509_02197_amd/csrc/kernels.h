@@ -143,8 +143,8 @@ hipError_t launch_finalize(const double* partials, int32_t nparts, double* loss,
 // (src may equal dst), and `sweeps` reverse sweeps applied to g in place.
 // With scratch (gs_pipe_bytes(s, n) bytes for some n >= sweeps, 128-byte
 // aligned) each runs as one persistent launch per 256 phases (gs_pipe.hip);
-// without (null), as a sequence of wavefront launches, one per level, that
-// pipelines the sweeps. gs_kernel_launches counts the levels. gs_pipe_bytes is
+// without (null), or where gs_takes_pipe is false, as a sequence of wavefront
+// launches, one per level, that pipelines the sweeps. gs_kernel_launches counts the levels. gs_pipe_bytes is
 // 0 where the persistent launch cannot run the shape.
 hipError_t launch_gs_forward(const StepShape& s, const void* src, void* dst, int32_t sweeps,
                              void* scratch, hipStream_t stream);
@@ -152,6 +152,7 @@ hipError_t launch_gs_adjoint(const StepShape& s, void* g, int32_t sweeps, void* 
                              hipStream_t stream);
 int64_t gs_kernel_launches(const StepShape& s, bool adjoint, int32_t sweeps);
 uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps);
+bool gs_takes_pipe(const StepShape& s, bool adjoint, int32_t sweeps);
 // The persistent launches of such a run, and the bytes they have to move.
 struct GsPipeCost {
   int64_t launches = 0;

@@ -79,6 +79,24 @@ def test_one_launch_gives_the_level_launches_bits(dtype, shape, T):
     assert rel(a[0], dx0) <= TOL[dtype] and abs(a[2] - L) <= TOL[dtype] * np.abs(aux * xT).sum()
 
 
+@pytest.mark.parametrize("dtype,shape,T,pipe", [
+    (F32, (400, 600), 1, False), (F32, (400, 600), 4, True), (F32, (2000, 2100), 3, False),
+    (F32, (2000, 2100), 5, True), (F32, (3000, 40), 1, True), (F64, (30, 40), 1, False),
+    (F64, (30, 40), 2, True), (F64, (400, 600), 1, True)])
+def test_short_forward_runs_take_the_faster_route(dtype, shape, T, pipe):
+    """A forward run of up to four sweeps goes by levels where they are the
+    faster; the reverse sweeps stay one launch. The bits are the same."""
+    r = np.random.Generator(np.random.PCG64(26))
+    x = dev(r.uniform(-1, 1, shape).astype(NP_DTYPE[dtype]))
+    a = adst.vjp(GS, x, None, T, flags=adst.ADST_TRACE)
+    names = {k["name"] for k in adst.adst_trace_kernels() if k["name"].startswith("gs_")}
+    assert names == {"gs_pipe<fwd>" if pipe else "gs_wave<fwd>", "gs_pipe<adj>"}
+    b = adst.vjp(GS, x, None, T, scratch=False)
+    for key in ("xT", "dx0", "loss"):
+        assert np.array_equal(a[key].cpu().numpy(), b[key].cpu().numpy()), key
+    assert np.array_equal(a["xT"].cpu().numpy(), oracle.forward(GS, x.cpu().numpy(), steps=T))
+
+
 def test_values_that_are_not_finite():
     r = np.random.Generator(np.random.PCG64(22))
     x, aux = r.uniform(-1, 1, (90, 300)), r.standard_normal((90, 300))
