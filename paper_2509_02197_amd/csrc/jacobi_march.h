@@ -159,37 +159,36 @@ inline bool make_grid_fit(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks,
   return true;
 }
 
-// The V elements from column c0 (a multiple of V) of the row at src, by one
-// 16-byte load clamped into the row. VEC: nx is a multiple of V and rows
-// are 16-byte aligned, so a block is in the grid or outside it; else the load
-// is at element alignment, and the block that holds the row's end is loaded
-// from column nx - V and its elements moved to their places. INNER: c0 .. c0 + V - 1 lie in the grid. With one load per
-// element in such rows, the waves waited on four times as many (a 2501 x 3003
-// f32 call of 60 steps with dL/dw: 4.21 -> 3.51 ms). NT: the non-temporal hint.
+// The V elements from column c0 (a multiple of V) of the row at src, those
+// outside the row with any value. VEC: nx is a multiple of V and rows are
+// 16-byte aligned, so a block is in the grid or outside it and one 16-byte load,
+// clamped into the row, brings it. INNER: c0 .. c0 + V - 1 lie in the grid; one
+// 16-byte load at element alignment where rows are not aligned (with one load
+// per element, the waves waited on four times as many: a 2501 x 3003 f32 call of
+// 60 steps with dL/dw, 4.21 -> 3.51 ms). Elsewhere one load per element,
+// clamped: nothing may touch a value before it enters the pipeline, and with
+// one load and its elements moved to their places here, every row of the first
+// and last strip waited for its own load (calls of 24 steps with dL/dw, so
+// against as it is: 500 x 127 f64 606 and 278 us, 400 x 401 f32 668 and 343;
+// moved on entry instead, plain f32 calls took 1.07 times as long as now). NT:
+// the non-temporal hint.
 template <class R, bool VEC, bool INNER, bool NT>
 __device__ inline void load_block(const R* src, int c0, int nx, R* out) {
   constexpr int V = 16 / sizeof(R);
   typedef R vec_t __attribute__((ext_vector_type(V), aligned(VEC ? 16 : sizeof(R))));
-  if (!VEC && !INNER && nx < V) {  // no whole block in a row (uniform)
+  if constexpr (!VEC && !INNER) {
 #pragma unroll
     for (int e = 0; e < V; ++e) out[e] = src[min(max(c0 + e, 0), nx - 1)];
-    return;
-  }
-  const int cc = INNER && !VEC ? c0 : min(max(c0, 0), nx - V);
-  const vec_t* p = reinterpret_cast<const vec_t*>(src + cc);
-  vec_t t;
-  if constexpr (NT)
-    t = __builtin_nontemporal_load(p);
-  else
-    t = *p;
+  } else {
+    const int cc = VEC ? min(max(c0, 0), nx - V) : c0;
+    const vec_t* p = reinterpret_cast<const vec_t*>(src + cc);
+    vec_t t;
+    if constexpr (NT)
+      t = __builtin_nontemporal_load(p);
+    else
+      t = *p;
 #pragma unroll
-  for (int e = 0; e < V; ++e) out[e] = t[e];
-  if constexpr (!VEC && !INNER) {
-    const int sh = c0 - cc;  // 1 .. V-1 in the block that holds the row's end
-#pragma unroll
-    for (int d = 1; d < V; d *= 2)
-#pragma unroll
-      for (int e = 0; e + d < V; ++e) out[e] = (sh > 0 && (sh & d)) ? out[e + d] : out[e];
+    for (int e = 0; e < V; ++e) out[e] = t[e];
   }
 }
 

@@ -41,7 +41,10 @@ def at_offset(a, off):
 # strip and several (124 or 248 columns, 240 to 256), the row's end in a
 # strip's first and last blocks
 SHAPES = [(F64, (40, 1)), (F64, (9, 125)), (F64, (70, 247)), (F64, (33, 501)), (F32, (30, 3)),
-          (F32, (25, 5)), (F32, (61, 249)), (F32, (40, 254)), (F32, (90, 751)), (F32, (20, 1023))]
+          (F32, (25, 5)), (F32, (61, 249)), (F32, (40, 254)), (F32, (90, 751)), (F32, (20, 1023)),
+          # rows of whole blocks: aligned ones from the buffer's start, off the
+          # 16-byte grid from its second element
+          (F64, (33, 500)), (F64, (15, 2)), (F32, (40, 752)), (F32, (61, 248)), (F32, (12, 4))]
 OPTS = [("plain", {}), ("dp", {"want_dparams": True}), ("lim", {"lim": (0.3, 0.7)})]
 
 
