@@ -112,10 +112,7 @@ adst_status check_problem(const adst_problem* p, int32_t grads, Checked* out) {
   out->fuse_fwd = fuse_steps ? max_fused_forward(p->kind) : 1;
   out->fuse_adj = fuse ? max_fused_adjoint(p->kind, p->n[0]) : 1;
   out->in_place = p->kind == ADST_GAUSSSEIDEL2D5;
-  // Jacobi grids of a few workgroups keep a launch (and its bytes in the plan)
-  // per kept state: there a launch is its latency, not its bytes.
-  const bool store = fuse_steps && (p->kind != ADST_JACOBI2D5 || n >= kJacStorePoints);
-  out->store_fwd = store ? max_stored_forward(p->kind) : 1;
+  out->store_fwd = fuse_steps ? max_stored_forward(p->kind) : 1;
   out->fuse_adj_fwd = fuse && p->kind == ADST_ALLENCAHN3D7 && ac_fuses_forward_adjoint(out->shape);
   out->pair_adj = fuse && jacobi_pairs_adjoint(out->shape, want_dp);
   // Allen-Cahn: two 2-step launches take less time than a 3-step launch and

@@ -246,9 +246,24 @@ hipError_t pair_launch(const StepShape& s, const R* x1, const R* x2, const R* g,
 
 }  // namespace
 
+// Times of 20 adjoint steps as pairs against single launches: f64 under the
+// limiter 0.74 to 0.98 from 8 x 8 to 2500 x 3003, thin grids among them. In
+// f32 the pair's general form, which masks columns and rows, takes longer than
+// two single steps': under the limiter 1.04 to 1.34 on grids of up to 8 rows
+// (all of them near an edge), 0.82 to 0.98 from 16 x 16 on; with dL/dw, whose
+// chunks are long, 1.13 to 1.27 where an interior strip reaches the last
+// columns or there is none (16 x 16 to 400 x 400, 5000 x 48, 128 x 500), 1.3 on
+// grids of one or two rows, 0.85 to 0.89 elsewhere (700 x 700, 48 x 5000, 2500 x
+// 3003).
 bool jacobi_pairs_adjoint(const StepShape& s, bool dparams) {
-  if (s.kind != ADST_JACOBI2D5 || int64_t(s.nx) * s.ny < kJacStorePoints) return false;
-  return dparams ? !s.limit && s.dtype == ADST_F32 : s.limit != 0;
+  if (s.kind != ADST_JACOBI2D5) return false;
+  if (!(dparams ? !s.limit && s.dtype == ADST_F32 : s.limit != 0)) return false;
+  if (s.dtype == ADST_F64) return true;
+  if (s.ny <= 2 * kEndRows) return false;
+  if (!dparams) return true;
+  constexpr int V = 16 / (int)sizeof(float), OW = kLanes * V - 2 * kPairH;
+  const int last = (s.nx + OW - 1) / OW - 2;  // the last interior strip
+  return last >= 1 && int64_t(last) * OW - kPairH + kLanes * V <= s.nx - 2;
 }
 
 hipError_t launch_jacobi_pair_adjoint(const StepShape& s, const void* x1, const void* x2,

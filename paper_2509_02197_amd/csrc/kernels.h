@@ -59,7 +59,6 @@ hipError_t launch_forward_n(const StepShape& s, const void* x, const void* K, vo
 // The ys are distinct and none overlaps x. Not the in-place kind; with the
 // limiter Jacobi only.
 constexpr int32_t kJacMaxStore = 4;
-constexpr int64_t kJacStorePoints = 1024;  // on grids of fewer points, no such runs
 constexpr int32_t kMaxStoredRun = kJacMaxStore > kAcMaxFuse ? kJacMaxStore : kAcMaxFuse;
 int32_t max_stored_forward(int32_t kind);
 hipError_t launch_forward_store(const StepShape& s, const void* x, const void* K, void* const* ys,

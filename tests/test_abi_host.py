@@ -168,8 +168,9 @@ def test_gradient_mask():
     S = 8 * 8 * 8
     stride = -(-S // 4096) * 4096
     assert withp.workspace_bytes == 16384 + (3 + 3) * stride + 4096
-    # bytes: every adjoint step also reads x_{t-1} for the partials
-    assert withp.alg_bytes - (16 * 5 + 16 * 5 + 16) * 64 == 8 * 5 * 64
+    # bytes: every adjoint step also reads x_{t-1} for the partials, and the four
+    # kept states are written by one launch that reads x0 once
+    assert withp.alg_bytes - (16 * 5 - 8 * 3 + 16 * 5 + 16) * 64 == 8 * 5 * 64
     # slot counts follow the adjoint's work items: Jacobi one per column strip
     # (124 columns in f64) and row chunk (12 rows in the two edge strips, 128
     # in the others, 6 at each end), Allen-Cahn 64 x 8 x 32 tiles, variable
