@@ -153,7 +153,8 @@ typedef struct {
   int32_t kind;   /* adst_kind */
   int32_t dtype;  /* adst_dtype */
   int64_t n[3];   /* n[0] = nx (fastest), n[1] = ny, n[2] = nz (1 for the 2-D kinds);
-                     every n[i] >= 1 and n[0]*n[1]*n[2] < 2^31 */
+                     every n[i] >= 1 and n[0]*n[1]*n[2] < 2^31; n[0] at
+                     most 2^31 - 1025 for JACOBI2D5 and VARDIFF2D9 */
   double p[2];    /* step constants, see the kinds above; rounded to the working precision */
   double lim[2];  /* limiter bounds lo <= hi (with ADST_LIMIT; rounded likewise) */
   uint32_t flags; /* ADST_FORCE_TAPE | ADST_TRACE | ADST_NO_FUSE | ADST_LIMIT */

@@ -77,6 +77,11 @@ adst_status check_problem(const adst_problem* p, int32_t grads, Checked* out) {
   if (n >= (int64_t(1) << 31)) return fail(ADST_ERR_ARG, "grid must have fewer than 2^31 points");
   if (p->kind != ADST_ALLENCAHN3D7 && p->n[2] != 1)
     return fail(ADST_ERR_UNSUPPORTED, "this kind is 2-D: n[2] must be 1");
+  // The tiles and marches of the 2-D kinds compute columns in 32 bits up to a
+  // tile or strip (256) beyond the row's end; in longer rows those would wrap
+  // to negative ones, which pass for columns of the grid.
+  if ((p->kind == ADST_JACOBI2D5 || p->kind == ADST_VARDIFF2D9) && p->n[0] > INT32_MAX - 1024)
+    return fail(ADST_ERR_UNSUPPORTED, "n[0] must be at most 2^31 - 1025 for this kind");
   // Every launch covers the grid with workgroups of 256 work-items: tiles of
   // 240 to 256 columns by 4 or 8 rows for the 2-D kinds, columns of 56 to 64
   // by 8 to 16 points over 32 to 256 planes for the 3-D kind. The work-item

@@ -98,6 +98,11 @@ def test_plan_rejects_unsupported_combinations():
         adst.ADST_ERR_UNSUPPORTED
     assert _status(adst.adst_plan, _p(adst.ADST_VARDIFF2D9, (8, 8, 3)), 5, 0, 0) == \
         adst.ADST_ERR_UNSUPPORTED
+    # rows whose last tile or strip would reach beyond 32-bit columns
+    for kind in (adst.ADST_JACOBI2D5, adst.ADST_VARDIFF2D9):
+        assert _status(adst.adst_plan, _p(kind, (2**31 - 1, 1, 1)), 5, 0, 0) == \
+            adst.ADST_ERR_UNSUPPORTED
+        assert adst.adst_plan(_p(kind, (2**31 - 1025, 1, 1)), 5, 0, 0).steps == 5
     # a coefficient gradient for a kind without a coefficient field
     assert _status(adst.adst_plan, _p(), 5, 0, 0, True) == adst.ADST_ERR_UNSUPPORTED
 
