@@ -142,11 +142,11 @@ def test_the_callers_workspace_and_scratch_are_the_ones_used():
     for scratch, used in ((None, extra), (mine, extra), (False, 0)):
         torch.cuda.synchronize()
         torch.cuda.reset_peak_memory_stats()
-        before = torch.cuda.memory_allocated()
+        before = torch.cuda.memory_stats()["requested_bytes.all.current"]
         out = adst.vjp(GS, x, None, T, budget_bytes=budget, sched=adst.ADST_SCHED_BINOMIAL,
                        flags=flags, ws=ws, scratch=scratch)
         torch.cuda.synchronize()
-        taken = torch.cuda.max_memory_allocated() - before
+        taken = torch.cuda.memory_stats()["requested_bytes.all.peak"] - before
         assert out["ws"] is ws and out["scratch_bytes"] == used
         assert taken <= 2 * x.nbytes + (extra if scratch is None else 0) + 4096, taken
         assert np.array_equal(out["xT"].cpu().numpy(), ref)

@@ -10,7 +10,7 @@ import pytest
 
 import oracle
 import paper_2509_02197_amd as adst
-from tests.gpu_util import NP_DTYPE, TOL, dev, gpu_vjp, rel, say
+from tests.gpu_util import NP_DTYPE, TOL, check_dw, dev, gpu_vjp, rel, say
 
 pytestmark = pytest.mark.gpu
 
@@ -77,3 +77,5 @@ def test_runs(dtype, shape, name, opt, T, slots, sched):
                                    aux=inp["aux"], want_dp=True, lim=opt.get("lim"))
     assert np.array_equal(a["xT"], xT)
     assert rel(a["dx0"], dx0) <= TOL[dtype]
+    if name == "dp":
+        check_dw(J, inp, T, a["dparams"], dp, TOL[dtype])

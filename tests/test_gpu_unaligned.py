@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import paper_2509_02197_amd as adst
-from tests.gpu_util import NP_DTYPE, TOL, rel, say
+from tests.gpu_util import NP_DTYPE, TOL, check_dw, rel, say
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,5 @@ def test_rows_off_the_16_byte_grid(kind, dtype, shape, name, opt):
     assert rel(outs[0]["dx0"], dx0) <= TOL[dtype]
     if dK:
         assert rel(outs[0]["dK"], gK) <= TOL[dtype]
+    if name == "dp":
+        check_dw(kind, {"x0": x, "K": K, "aux": aux}, T, outs[0]["dparams"], dp, TOL[dtype])
