@@ -182,17 +182,22 @@ uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps) {
 // Whether a run takes the persistent launch where it has the scratch for it.
 // A forward run of a few sweeps may be shorter as levels, in f32 above all,
 // where a strip is twice as wide and its clock longer: the launch takes about
-// 10 us and 0.32 (f64 0.24) us for each of its clocks, 0.26 (0.21) where it is
-// one strip; a level of that few tiles takes 9 us. Forward runs as one launch
-// and as levels, us: 5000 x 5000 f32 one sweep 2366 and 1978, three 2386 and
-// 2078, eight 2399 and 2488; 400 x 400 f32 one 187 and 161, three 189 and 218;
-// 32 x 32 f64 one 34 and 29, two 33 and 53; 400 x 400 f64 one 184 and 207. The
-// reverse sweeps were the faster as one launch at all sizes (0.31 to 0.97).
+// 10 us and, for each of its clocks, 0.24 us in f64 and 0.29 to 0.34 in f32, as
+// the rows grow in number (0.21 and 0.26 where it is one strip); a level of
+// that few tiles of aligned rows takes 9 us (of others a third more). Forward
+// runs as one launch and as levels, us: 5000 x 5000 f32 one sweep 2366 and
+// 1978, three 2386 and 2078, eight 2399 and 2488; 2048 x 2048 f32 five 1000 and
+// 908; 400 x 400 f32 one 187 and 161, three 189 and 218; 1501 x 2003 f32 one
+// 767 and 1046; 32 x 32 f64 one 34 and 29, two 33 and 53; 400 x 400 f64 one 184
+// and 207. The reverse sweeps were the faster as one launch at all sizes (0.31
+// to 0.97).
 bool gs_takes_pipe(const StepShape& s, bool adjoint, int32_t sweeps) {
-  if (adjoint || sweeps > 4) return true;
   const bool f64 = s.dtype == ADST_F64;
+  if (adjoint || sweeps > 6 || s.nx % (f64 ? 2 : 4) != 0) return true;
   const int64_t strips = gp_geom(s, 1, kGpNarrow).ncol, clocks = int64_t(s.ny) + 76 + 88 * (strips - 1);
-  const double clock = strips == 1 ? (f64 ? 0.21 : 0.26) : (f64 ? 0.24 : 0.32);
+  const double clock = strips == 1 ? (f64 ? 0.21 : 0.26)
+                       : f64      ? 0.24
+                                  : 0.29 + 0.05 * std::min(1.0, s.ny / 1000.0);
   return 9.0 * double(gs_kernel_launches(s, false, sweeps)) >= 10.0 + clock * double(clocks);
 }
 

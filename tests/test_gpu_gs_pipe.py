@@ -81,11 +81,12 @@ def test_one_launch_gives_the_level_launches_bits(dtype, shape, T):
 
 @pytest.mark.parametrize("dtype,shape,T,pipe", [
     (F32, (400, 600), 1, False), (F32, (400, 600), 4, True), (F32, (2000, 2100), 3, False),
-    (F32, (2000, 2100), 5, True), (F32, (3000, 40), 1, True), (F64, (30, 40), 1, False),
-    (F64, (30, 40), 2, True), (F64, (400, 600), 1, True)])
+    (F32, (2000, 2100), 7, True), (F32, (2000, 2101), 1, True), (F32, (3000, 40), 1, True),
+    (F64, (30, 40), 1, False), (F64, (30, 41), 1, True), (F64, (30, 40), 2, True),
+    (F64, (400, 600), 1, True)])
 def test_short_forward_runs_take_the_faster_route(dtype, shape, T, pipe):
-    """A forward run of up to four sweeps goes by levels where they are the
-    faster; the reverse sweeps stay one launch. The bits are the same."""
+    """A forward run of up to six sweeps goes by levels where they are the
+    faster (aligned rows only); the reverse sweeps stay one launch. The bits are the same."""
     r = np.random.Generator(np.random.PCG64(26))
     x = dev(r.uniform(-1, 1, shape).astype(NP_DTYPE[dtype]))
     a = adst.vjp(GS, x, None, T, flags=adst.ADST_TRACE)
