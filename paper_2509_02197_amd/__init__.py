@@ -372,9 +372,10 @@ def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, f
     prob = make_problem(kind, _dtype_code(x0), _dims(x0.shape), params, flags, lim)
     xT = torch.empty_like(x0)
     info = adst_plan(prob, steps, 1 << 62, ADST_SCHED_STORE_ALL)
-    ws = _device_bytes(max(info.fwd_workspace_bytes, 1), x0.device, stream)
+    need = info.fwd_workspace_bytes
+    ws = _device_bytes(need, x0.device, stream) if need else None
     scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
-    adst_forward(prob, x0, coeff, steps, xT, ws, info.fwd_workspace_bytes, stream, scratch,
+    adst_forward(prob, x0, coeff, steps, xT, ws, need, stream, scratch,
                  0 if scratch is None else scratch.nbytes)
     return xT
 
