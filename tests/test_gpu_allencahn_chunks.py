@@ -9,7 +9,7 @@ import pytest
 
 import oracle
 import paper_2509_02197_amd as adst
-from tests.gpu_util import NP_DTYPE, TOL, gpu_vjp, rel, say
+from tests.gpu_util import NP_DTYPE, TOL, dev, gpu_vjp, rel, say
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +42,13 @@ def test_short_chunks(dtype, shape, lim):
                                lim=lim)
     assert np.array_equal(a["xT"], xT)
     assert rel(a["dx0"], dx0) <= TOL[dtype]
+
+
+def test_one_step_on_a_grid_of_four_workgroups_a_cu():
+    """1024 tiles of 32 planes: f64 single steps keep them, f32 ones take 16."""
+    r = np.random.Generator(np.random.PCG64(62))
+    x = r.uniform(-1.0, 1.0, (33, 256, 1024))
+    for a in (x[:32], x, x[:32].astype(np.float32)):
+        for lim in (None, (-0.6, 0.7)):
+            got = adst.forward(AC, dev(a), None, 1, lim=lim).cpu().numpy()
+            assert np.array_equal(got, oracle.forward(AC, a, steps=1, lim=lim))
