@@ -148,9 +148,20 @@ constexpr int kFillWaves = 2048;
 // Jacobi call, T = 10: 46.9 -> 42.7 us; 120 x 118 f32 variable coefficients
 // with dK, T = 20: 442 -> 361).
 constexpr int kFewWaves = 512;
-inline bool make_grid_fit(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows = kRows) {
+// Jacobi launches of several steps evaluate up to twelve rows beyond a chunk, as
+// many as the shortest chunk has, so they take chunks of less than 2 *
+// kEdgeRows only where the interior strips have fewer chunks than this (calls of
+// 36 steps, us, 24 and 12 rows: f64 1400^2 188 and 210, 2048^2 284 and 301 with
+// 285 at 48, 1000^2 178 and 172, 500^2 164 and 149, 4096 x 500 222 and 211, under
+// the limiter 2048^2 1113 and 1206, 1000^2 527 and 473; f32 2500^2 257 and 281,
+// 14 limited forward steps at 2048^2 61 and 53).
+template <class R>
+constexpr int kJacShort = sizeof(R) == 8 ? 550 : 700;
+inline bool make_grid_fit(int nx, int ny, int ow, MarchGrid* g, int64_t* blocks, int rows,
+                          int short_below) {
   if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
   while (rows > kEdgeRows && *blocks < kFillWaves) {
+    if (rows / 2 < 2 * kEdgeRows && int64_t(g->ns - g->nedge) * g->ci >= short_below) break;
     rows = rows / 2 < kEdgeRows ? kEdgeRows : rows / 2;
     if (!make_grid(nx, ny, ow, g, blocks, rows)) return false;
   }

@@ -62,7 +62,7 @@ hipError_t march_launch(const StepShape& s, const R* x, R* y, hipStream_t st) {
   if (ADJ && s.nx <= G::V) return hipErrorInvalidValue;  // a lane would hold both ring columns
   MarchGrid g;
   int64_t blocks;
-  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks)) return hipErrorInvalidValue;
+  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks, kRows, kJacShort<R>)) return hipErrorInvalidValue;
   if (rows_aligned<R>(s.nx, x, y))
     jacobi_march<R, K, ADJ, true><<<dim3((unsigned)blocks), dim3(kLanes), 0, st>>>(
         x, y, s.nx, s.ny, g, R(s.p0), {});
@@ -264,7 +264,7 @@ hipError_t lim_adjoint_launch(const StepShape& s, const R* x, const R* g, R* gp,
   int64_t blocks;
   // the slots of dL/dw belong to chunks of kLimRows
   if (!(dp_part ? make_grid(s.nx, s.ny, OW, &grid, &blocks, kLimRows)
-                : make_grid_fit(s.nx, s.ny, OW, &grid, &blocks, kLimRows)))
+                : make_grid_fit(s.nx, s.ny, OW, &grid, &blocks, kLimRows, kJacShort<R>)))
     return hipErrorInvalidValue;
   const bool vec = rows_aligned<R>(s.nx, x, g) && rows_aligned<R>(s.nx, gp, nullptr);
   const dim3 gr((unsigned)blocks), bl(kLanes);

@@ -19,7 +19,7 @@ hipError_t lim_launch(const StepShape& s, const R* x, R* y, hipStream_t st) {
   using G = Geom<R, K>;
   MarchGrid g;
   int64_t blocks;
-  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks)) return hipErrorInvalidValue;
+  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks, kRows, kJacShort<R>)) return hipErrorInvalidValue;
   const MarchExtra<R, K, true, false> ex{{R(s.lo), R(s.hi)}, {nullptr}};
   const dim3 grid((unsigned)blocks), block(kLanes);
   if (rows_aligned<R>(s.nx, x, y))

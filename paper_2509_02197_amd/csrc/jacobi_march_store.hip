@@ -17,7 +17,7 @@ hipError_t store_launch(const StepShape& s, const R* x, void* const* ys, hipStre
   using G = Geom<R, K>;
   MarchGrid g;
   int64_t blocks;
-  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks)) return hipErrorInvalidValue;
+  if (!make_grid_fit(s.nx, s.ny, G::OW, &g, &blocks, kRows, kJacShort<R>)) return hipErrorInvalidValue;
   MarchExtra<R, K, LIM, true> ex{};
   ex.lim = {R(s.lo), R(s.hi)};
   R* y = static_cast<R*>(ys[K - 1]);

@@ -217,7 +217,7 @@ hipError_t pair_launch(const StepShape& s, const R* x1, const R* x2, const R* g,
   int64_t blocks;
   // the slots of dL/dw belong to chunks of kLimRows
   if (!(dp_part ? make_grid(s.nx, s.ny, OW, &grid, &blocks, kLimRows)
-                : make_grid_fit(s.nx, s.ny, OW, &grid, &blocks, kPairRows)))
+                : make_grid_fit(s.nx, s.ny, OW, &grid, &blocks, kPairRows, kJacShort<R>)))
     return hipErrorInvalidValue;
   const bool vec = rows_aligned<R>(s.nx, x1, x2) && rows_aligned<R>(s.nx, g, gp);
   const dim3 gr((unsigned)blocks), bl(kLanes);

@@ -209,7 +209,7 @@ hipError_t vd_run(const StepShape& s, const R* x, const R* K, R* y, R* mid, hipS
   constexpr int V = 16 / (int)sizeof(R), OW = kLanes * V - 2 * V;
   MarchGrid g;
   int64_t blocks;
-  if (!make_grid_fit(s.nx, s.ny, OW, &g, &blocks, mid ? kVdStoreRows : kVdRows))
+  if (!make_grid_fit(s.nx, s.ny, OW, &g, &blocks, mid ? kVdStoreRows : kVdRows, INT32_MAX))
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks), block(kLanes);
   const R dt = R(s.p0), ca = R(1) / R(3), cd = R(1) / R(12);

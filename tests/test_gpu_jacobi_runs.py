@@ -79,3 +79,19 @@ def test_runs(dtype, shape, name, opt, T, slots, sched):
     assert rel(a["dx0"], dx0) <= TOL[dtype]
     if name == "dp":
         check_dw(J, inp, T, a["dparams"], dp, TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype,shape", [(F64, (700, 700)), (F64, (1400, 1403)),
+                                         (F32, (2100, 2604))])
+@pytest.mark.parametrize("opt", [{}, {"lim": LIM}, {"want_dparams": True}])
+def test_chunk_lengths(dtype, shape, opt):
+    """Interior chunks of 12, 24 and 48 rows: the bits of one launch per step."""
+    r = np.random.Generator(np.random.PCG64(84))
+    inp = {"x0": r.uniform(0, 1, shape).astype(NP_DTYPE[dtype]),
+           "aux": r.standard_normal(shape).astype(NP_DTYPE[dtype])}
+    kw = dict(budget=5 * inp["x0"].nbytes, sched=adst.ADST_SCHED_BINOMIAL, **opt)
+    a = gpu_vjp(J, inp, 13, adst.ADST_LOSS_DOT_W, **kw)
+    b = gpu_vjp(J, inp, 13, adst.ADST_LOSS_DOT_W, flags=adst.ADST_NO_FUSE, **kw)
+    for key in ("dx0", "xT", "dparams"):
+        if a[key] is not None:
+            assert np.array_equal(a[key], b[key]), key
