@@ -527,7 +527,7 @@ def rocprof_label(name):
                 (",store>" if len(targs) > 5 and t(5) else ">"))
     if base == "vd_march":             # <R, VEC, ST, NT>
         return "vd_march<store>" if t(2) else "vd_march"
-    if base in ("jacobi_lim_adjoint", "jacobi_pair_adjoint"):  # <R, VEC, DP>
+    if base in ("jacobi_lim_adjoint", "jacobi_pair_adjoint"):  # <R, VEC, DP, NT>
         return base + ("<dp>" if t(2) else "")
     if base in ("gs_wave", "gs_pipe"):  # <R, ADJ, ...>
         return base + ("<adj>" if t(1) else "<fwd>")

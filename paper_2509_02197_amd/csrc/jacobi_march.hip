@@ -87,7 +87,7 @@ hipError_t march_launch(const StepShape& s, const R* x, R* y, hipStream_t st) {
 // +x[S])+x[N]) (the forward's sum, in double), over the work item's output
 // points; a wave butterfly then adds it into the item's slot
 // (dp_part[item], or overwrites it on the step t = T).
-template <class R, bool VEC, bool DP>
+template <class R, bool VEC, bool DP, bool NT>
 __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict__ x,
                                                              const R* __restrict__ g,
                                                              R* __restrict__ gp, int nx, int ny,
@@ -118,11 +118,11 @@ __global__ __launch_bounds__(kLanes) void jacobi_lim_adjoint(const R* __restrict
   }
   const bool strip_in = s0 - H >= 2 && s0 - H + kLanes * V <= nx - 2;
   const bool st_lane = lane * V >= H && lane * V < H + OW;
-  // x and g are read once per step, with the non-temporal hint (4096^2
+  // x and g are read once per step, with the non-temporal hint (NT: 4096^2
   // f64: 90.5 -> 83.5 us per step; the hint on x alone did nothing)
   auto load = [&](const R* a, int row, R* out, auto inner_t) {
     const int rr = min(max(row, lo_need), hi_need);
-    load_block<R, VEC, decltype(inner_t)::value, true>(a + (int64_t)rr * nx, c0, nx, out);
+    load_block<R, VEC, decltype(inner_t)::value, NT>(a + (int64_t)rr * nx, c0, nx, out);
   };
   enum { kFast = 0, kGeneral = 2 };
   auto march = [&](auto dir_t, auto mid_t) {
@@ -270,18 +270,28 @@ hipError_t lim_adjoint_launch(const StepShape& s, const R* x, const R* g, R* gp,
   const dim3 gr((unsigned)blocks), bl(kLanes);
   const R w = R(s.p0), lo = R(s.lo), hi = R(s.hi);
   const int first = dp_first ? 1 : 0;
+  // Rows off the 16-byte grid share their lines between waves and rows: where
+  // two states fit the Infinity Cache, a line read without the hint is still
+  // there for the other reader (steps with dL/dw, calls of 24 steps, us, with and
+  // without: f64 1501 x 2003 1115 and 985, 3001 x 3003 1981 and 1950, 5001 x 5003
+  // 4903 and 5477; under the limiter too f32 3001 x 3003 1981 and 1836).
+  const bool nt = vec || int64_t(s.nx) * s.ny * int64_t(sizeof(R)) >= kStreamBytes / 2;
+#define ADST_LIM_ADJ(VECV, DPV, NTV)                                                     \
+  jacobi_lim_adjoint<R, VECV, DPV, NTV><<<gr, bl, 0, st>>>(x, g, gp, s.nx, s.ny, grid, w, \
+                                                           lo, hi, dp_part, first)
   if (dp_part && vec)
-    jacobi_lim_adjoint<R, true, true><<<gr, bl, 0, st>>>(x, g, gp, s.nx, s.ny, grid, w, lo, hi,
-                                                         dp_part, first);
+    ADST_LIM_ADJ(true, true, true);
+  else if (dp_part && nt)
+    ADST_LIM_ADJ(false, true, true);
   else if (dp_part)
-    jacobi_lim_adjoint<R, false, true><<<gr, bl, 0, st>>>(x, g, gp, s.nx, s.ny, grid, w, lo, hi,
-                                                          dp_part, first);
+    ADST_LIM_ADJ(false, true, false);
   else if (vec)
-    jacobi_lim_adjoint<R, true, false><<<gr, bl, 0, st>>>(x, g, gp, s.nx, s.ny, grid, w, lo, hi,
-                                                          nullptr, 0);
+    ADST_LIM_ADJ(true, false, true);
+  else if (nt)
+    ADST_LIM_ADJ(false, false, true);
   else
-    jacobi_lim_adjoint<R, false, false><<<gr, bl, 0, st>>>(x, g, gp, s.nx, s.ny, grid, w, lo,
-                                                           hi, nullptr, 0);
+    ADST_LIM_ADJ(false, false, false);
+#undef ADST_LIM_ADJ
   return hipGetLastError();
 }
 

@@ -29,7 +29,7 @@ constexpr int kPairH = 4;
 constexpr int kPairAhead = 3;  // six rows ahead: no faster in f64, 13% slower in f32
 constexpr int kPairRows = 192;  // 128: 119.5 against 114.6 us at 4096^2 f64, 64: 121.7
 
-template <class R, bool VEC, bool DP>
+template <class R, bool VEC, bool DP, bool NT>
 __global__ __launch_bounds__(kLanes) void jacobi_pair_adjoint(
     const R* __restrict__ x1, const R* __restrict__ x2, const R* __restrict__ g,
     R* __restrict__ gp, int nx, int ny, MarchGrid grid, R w, R lo, R hi, double* dp_part,
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kLanes) void jacobi_pair_adjoint(
     const int ifirst = DIR > 0 ? r0 - 3 : r1 + 2;  // row of input index 0
     auto load = [&](const R* a, int row, R* out) {
       const int rr = min(max(row, lo_need), hi_need);
-      load_block<R, VEC, INNER, true>(a + (int64_t)rr * nx, c0, nx, out);
+      load_block<R, VEC, INNER, NT>(a + (int64_t)rr * nx, c0, nx, out);
     };
     // slot p mod 3 holds pipeline index p (row ifirst + DIR*p); xw2's is of
     // the index its row enters at, one later
@@ -223,24 +223,33 @@ hipError_t pair_launch(const StepShape& s, const R* x1, const R* x2, const R* g,
   const dim3 gr((unsigned)blocks), bl(kLanes);
   const R w = R(s.p0), lo = R(s.lo), hi = R(s.hi);
   const int first = dp_first ? 1 : 0;
+  // the hint as for the single step (lim_adjoint_launch), with four states
+  // (limited calls of 24 steps, us, with and without: f64 2049 x 2049 764 and 722,
+  // 3001 x 3003 1472 and 1521; f32 3001 x 3003 869 and 836, 5001 x 5003 2101 and
+  // 2253)
+  const bool nt = vec || int64_t(s.nx) * s.ny * int64_t(sizeof(R)) >= kStreamBytes / 4;
+#define ADST_PAIR(VECV, DPV, NTV)                                                              \
+  jacobi_pair_adjoint<R, VECV, DPV, NTV><<<gr, bl, 0, st>>>(x1, x2, g, gp, s.nx, s.ny, grid, w, \
+                                                            lo, hi, dp_part, first)
   if (dp_part) {
     if constexpr (V == kPairH) {  // the single step's work items
       if (vec)
-        jacobi_pair_adjoint<R, true, true><<<gr, bl, 0, st>>>(x1, x2, g, gp, s.nx, s.ny, grid, w,
-                                                              lo, hi, dp_part, first);
+        ADST_PAIR(true, true, true);
+      else if (nt)
+        ADST_PAIR(false, true, true);
       else
-        jacobi_pair_adjoint<R, false, true><<<gr, bl, 0, st>>>(x1, x2, g, gp, s.nx, s.ny, grid, w,
-                                                               lo, hi, dp_part, first);
+        ADST_PAIR(false, true, false);
     } else {
       return hipErrorInvalidValue;
     }
   } else if (vec) {
-    jacobi_pair_adjoint<R, true, false><<<gr, bl, 0, st>>>(x1, x2, g, gp, s.nx, s.ny, grid, w, lo,
-                                                           hi, nullptr, 0);
+    ADST_PAIR(true, false, true);
+  } else if (nt) {
+    ADST_PAIR(false, false, true);
   } else {
-    jacobi_pair_adjoint<R, false, false><<<gr, bl, 0, st>>>(x1, x2, g, gp, s.nx, s.ny, grid, w,
-                                                            lo, hi, nullptr, 0);
+    ADST_PAIR(false, false, false);
   }
+#undef ADST_PAIR
   return hipGetLastError();
 }
 

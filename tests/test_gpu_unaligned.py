@@ -75,3 +75,25 @@ def test_rows_off_the_16_byte_grid(kind, dtype, shape, name, opt):
         assert rel(outs[0]["dK"], gK) <= TOL[dtype]
     if name == "dp":
         check_dw(kind, {"x0": x, "K": K, "aux": aux}, T, outs[0]["dparams"], dp, TOL[dtype])
+
+
+@pytest.mark.parametrize("dtype,shape", [(F64, (2901, 2903)), (F64, (4101, 4103)),
+                                         (F32, (4101, 4103)), (F32, (5801, 5803))])
+def test_odd_rows_beyond_the_cache(dtype, shape):
+    """States of 64 MiB and 128 MiB, from which the adjoints that read state
+    take the non-temporal hint on odd rows: dL/dw asked for or not, steps fused
+    or not, the same bits."""
+    say(f"odd rows beyond the cache dtype={dtype} shape={shape}")
+    import torch
+    x = torch.rand(*shape, dtype=torch.float64 if dtype == F64 else torch.float32, device="cuda")
+    aux = torch.randn_like(x)
+
+    def run(**kw):
+        return adst.vjp(J, x, None, 5, adst.ADST_LOSS_SEED, aux, 6 * x.nbytes,
+                        adst.ADST_SCHED_STORE_ALL, **kw)
+    plain, dp = run(), run(want_dparams=True)
+    assert torch.equal(plain["dx0"], dp["dx0"])
+    one = run(want_dparams=True, flags=adst.ADST_NO_FUSE)
+    assert torch.equal(one["dparams"], dp["dparams"])
+    a, b = run(lim=(0.3, 0.7)), run(lim=(0.3, 0.7), flags=adst.ADST_NO_FUSE)
+    assert torch.equal(a["dx0"], b["dx0"]) and torch.equal(a["xT"], b["xT"])
