@@ -182,7 +182,7 @@ uint64_t gs_pipe_bytes(const StepShape& s, int32_t sweeps) {
 // Whether a run takes the persistent launch where it has the scratch for it.
 // A forward run of a few sweeps may be shorter as levels, in f32 above all,
 // where a strip is twice as wide and its clock longer: the launch takes about
-// 10 us and, for each of its clocks, 0.24 us in f64 and 0.29 to 0.34 in f32, as
+// 10 us and, for each of its clocks, 0.24 us in f64 and 0.30 to 0.34 in f32, as
 // the rows grow in number (0.21 and 0.26 where it is one strip); a level of
 // that few tiles of aligned rows takes 9 us (of others a third more). Forward
 // runs as one launch and as levels, us: 5000 x 5000 f32 one sweep 2366 and
@@ -197,7 +197,7 @@ bool gs_takes_pipe(const StepShape& s, bool adjoint, int32_t sweeps) {
   const int64_t strips = gp_geom(s, 1, kGpNarrow).ncol, clocks = int64_t(s.ny) + 76 + 88 * (strips - 1);
   const double clock = strips == 1 ? (f64 ? 0.21 : 0.26)
                        : f64      ? 0.24
-                                  : 0.29 + 0.05 * std::min(1.0, s.ny / 1000.0);
+                                  : 0.30 + 0.04 * std::min(1.0, s.ny / 1000.0);
   return 9.0 * double(gs_kernel_launches(s, false, sweeps)) >= 10.0 + clock * double(clocks);
 }
 
