@@ -211,11 +211,13 @@ def adst_sweep_workspace_bytes(prob, steps):
 def adst_forward(prob, x0, coeff, steps, xT, ws, ws_bytes, stream=None, scratch=None,
                  scratch_bytes=0):
     """adst_forward, or with scratch adst_forward_scratch."""
-    args = [ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, _ptr(xT), _ptr(ws), ws_bytes]
     if scratch is None:
-        _check(lib().adst_forward(*args, _stream(stream)))
+        _check(lib().adst_forward(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, _ptr(xT),
+                                  _ptr(ws), ws_bytes, _stream(stream)))
     else:
-        _check(lib().adst_forward_scratch(*args, _ptr(scratch), scratch_bytes, _stream(stream)))
+        _check(lib().adst_forward_scratch(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps,
+                                          _ptr(xT), _ptr(ws), ws_bytes, _ptr(scratch),
+                                          scratch_bytes, _stream(stream)))
 
 
 def adst_vjp(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx0, dcoeff, xT,
@@ -223,14 +225,18 @@ def adst_vjp(prob, x0, coeff, steps, loss, loss_aux, mem_budget_bytes, sched, dx
              scratch_bytes=0):
     """adst_vjp, or with scratch adst_vjp_scratch."""
     info = adst_plan_info() if want_info else None
-    args = [ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, loss, _ptr(loss_aux),
-            mem_budget_bytes, sched, _ptr(dx0), _ptr(dcoeff), _ptr(xT), _ptr(loss_dev),
-            _ptr(dparams), _ptr(ws), ws_bytes]
-    last = [_stream(stream), ctypes.byref(info) if info is not None else None]
     if scratch is None:
-        _check(lib().adst_vjp(*args, *last))
+        _check(lib().adst_vjp(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, loss,
+                              _ptr(loss_aux), mem_budget_bytes, sched, _ptr(dx0), _ptr(dcoeff),
+                              _ptr(xT), _ptr(loss_dev), _ptr(dparams), _ptr(ws), ws_bytes,
+                              _stream(stream), ctypes.byref(info) if info is not None else None))
     else:
-        _check(lib().adst_vjp_scratch(*args, _ptr(scratch), scratch_bytes, *last))
+        _check(lib().adst_vjp_scratch(ctypes.byref(prob), _ptr(x0), _ptr(coeff), steps, loss,
+                                      _ptr(loss_aux), mem_budget_bytes, sched, _ptr(dx0),
+                                      _ptr(dcoeff), _ptr(xT), _ptr(loss_dev), _ptr(dparams),
+                                      _ptr(ws), ws_bytes, _ptr(scratch), scratch_bytes,
+                                      _stream(stream),
+                                      ctypes.byref(info) if info is not None else None))
     return info
 
 
@@ -348,7 +354,7 @@ def _sweep_scratch(scratch, prob, steps, device, stream):
     the caller's, or one taken from torch's allocator where that much is free
     (none for scratch=False)."""
     import torch
-    if prob.kind != ADST_GAUSSSEIDEL2D5 or scratch is False:
+    if scratch is False:
         return None
     if scratch is not None:
         if not torch.is_tensor(scratch) or scratch.device != device or \
@@ -374,9 +380,12 @@ def forward(kind, x0, coeff=None, steps=1, params=None, stream=None, lim=None, f
     info = adst_plan(prob, steps, 1 << 62, ADST_SCHED_STORE_ALL)
     need = info.fwd_workspace_bytes
     ws = _device_bytes(need, x0.device, stream) if need else None
-    scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
-    adst_forward(prob, x0, coeff, steps, xT, ws, need, stream, scratch,
-                 0 if scratch is None else scratch.nbytes)
+    if kind == ADST_GAUSSSEIDEL2D5:
+        scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
+        adst_forward(prob, x0, coeff, steps, xT, ws, need, stream, scratch,
+                     0 if scratch is None else scratch.nbytes)
+    else:
+        adst_forward(prob, x0, coeff, steps, xT, ws, need, stream)
     return xT
 
 
@@ -403,7 +412,8 @@ def vjp(kind, x0, coeff=None, steps=1, loss=ADST_LOSS_HALF_SQ, aux=None, budget_
     info = adst_plan(prob, steps, budget_bytes, sched, grads)
     if ws is None or ws.numel() < info.workspace_bytes:
         ws = _device_bytes(info.workspace_bytes, x0.device, stream)
-    scratch = _sweep_scratch(scratch, prob, steps, x0.device, stream)
+    scratch = (_sweep_scratch(scratch, prob, steps, x0.device, stream)
+               if kind == ADST_GAUSSSEIDEL2D5 else None)
     dx0 = torch.empty_like(x0)
     dK = torch.empty_like(x0) if want_dcoeff else None
     xT = torch.empty_like(x0) if want_xT else None
