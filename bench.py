@@ -258,7 +258,7 @@ def run_workload(adst, torch, w, opts, steps, warmup, traced_calls, say, inp=Non
     t0 = time.perf_counter()
     for e0, e1 in evs:
         e0.record(stream)
-        call(prob)
+        info = call(prob)  # the plan with the launches and bytes of the call itself
         e1.record(stream)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
